@@ -25,6 +25,7 @@
 // multiple of 64 is padded to whole 64-bit chunks), at most 32 taps.
 #include <type_traits>
 
+#include "fastdiv.hpp"
 #include "fp4_expand.hpp"
 #include "kernels.hpp"
 #include "lane_ops.hpp"
@@ -61,30 +62,6 @@ __device__ __forceinline__ void buf_load(uint32_t (&v)[VW], __amdgpu_buffer_rsrc
   } else {
     v[0] = __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0);
   }
-}
-
-// Unsigned division by a run-time invariant divisor d >= 1 with a multiply
-// and shifts (Granlund and Montgomery, "Division by invariant integers using
-// multiplication", 1994): exact for every 32-bit n.
-struct FastDiv {
-  uint32_t d, m;
-  int s1, s2;
-};
-
-inline FastDiv make_fastdiv(uint32_t d) {
-  int l = 0;
-  while ((uint64_t{1} << l) < d) ++l;  // l = ceil(log2 d)
-  FastDiv f;
-  f.d = d;
-  f.m = static_cast<uint32_t>(((uint64_t{1} << 32) * ((uint64_t{1} << l) - d)) / d + 1);
-  f.s1 = l < 1 ? l : 1;
-  f.s2 = l > 1 ? l - 1 : 0;
-  return f;
-}
-
-__device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) {
-  const uint32_t t = __umulhi(f.m, n);
-  return (t + ((n - t) >> f.s1)) >> f.s2;
 }
 
 struct Mfma32Args {
