@@ -30,4 +30,25 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) {
   return (t + ((n - t) >> f.s1)) >> f.s2;
 }
 
+// The same for n < 2^31 with two shifts and one multiply: m = ceil(2^(31 + s)
+// / d), s = ceil(log2 d), so m d - 2^(31 + s) < d <= 2^s and the error of
+// 2 n m / 2^(32 + s) against n / d stays below 1 / d.
+struct FastDiv31 {
+  uint32_t d, m;
+  int s;
+};
+
+inline FastDiv31 make_fastdiv31(uint32_t d) {
+  FastDiv31 f;
+  f.d = d;
+  f.s = 0;
+  while ((uint64_t{1} << f.s) < d) ++f.s;
+  f.m = static_cast<uint32_t>(((uint64_t{1} << (31 + f.s)) + d - 1) / d);
+  return f;
+}
+
+__device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv31& f) {
+  return __umulhi(n << 1, f.m) >> f.s;
+}
+
 }  // namespace bnn
