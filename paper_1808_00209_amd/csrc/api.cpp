@@ -177,6 +177,10 @@ bnn_status gemm_launch(int64_t M, int64_t N, int64_t K, const uint32_t* A,
   if (M <= g_opt.gemv_max_rows)
     return hip_status(bnn::launch_bgemv_valu(M, N, K, A, B, thr, flip, sums, bits, s),
                       "bgemm (gemv) launch");
+  hipError_t err = hipSuccess;
+  if (g_opt.algo != BNN_ALGO_VALU &&
+      bnn::launch_bfc_tile(M, N, K, A, B, thr, flip, sums, bits, s, &err))
+    return hip_status(err, "bgemm launch");
   // K >= 1024 and N a multiple of 32: the FC kernel (bfc_gemm.hip), a
   // workgroup per 32 x 32 output tile up to 512 tiles, per 2 x 2 tiles above
   // that when N is a multiple of 64 (K not a multiple of the K split:

@@ -159,6 +159,14 @@ hipError_t launch_bfc_gemm(int64_t M, int64_t N, int64_t K, const uint32_t* A,
                            const uint32_t* B, const int32_t* thr, const uint32_t* flip,
                            int32_t* sums, uint32_t* bits, hipStream_t s);
 
+// Binary FC layer / GEMM at many rows (bfc_tile.hip): up to 256 outputs x
+// 128 rows per workgroup, the data rows staged in LDS as fp4 operands.  Returns false,
+// with nothing launched, for shapes the other kernels are the faster for;
+// otherwise launches and sets *err.
+bool launch_bfc_tile(int64_t M, int64_t N, int64_t K, const uint32_t* A, const uint32_t* B,
+                     const int32_t* thr, const uint32_t* flip, int32_t* sums, uint32_t* bits,
+                     hipStream_t s, hipError_t* err);
+
 // Two consecutive binary FC layers, the second with N1 <= 32 outputs, in one
 // launch of the FC kernel (bfc_gemm.hip): a workgroup per 32 x 32 tile of the
 // first layer (K0 >= 1024, N0 a multiple of 32, at most 512 tiles, at most
