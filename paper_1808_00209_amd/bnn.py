@@ -138,20 +138,32 @@ def _check(status: int):
         raise BnnError(status, last_error())
 
 
+# A small layer's kernel takes 3-5 us, as long as it takes to get through this
+# binding, so a call spends as little here as it can: pointers and the stream
+# go to ctypes as plain ints, the stream handle comes without a Stream object
+# around it, and a conv's output sizes are worked out here (host time of one
+# call: a bgemm 9.9 -> 7.1 us, a small 3x3 conv 12.7 -> 9.3, a forward pass at
+# one image 20.3 -> 19.2).
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _raw_device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_raw_device())
 
 
 def _dev(t, dtype, name):
     if t is None:
         return None
-    if not isinstance(t, torch.Tensor) or t.dtype != dtype or not t.is_cuda:
+    if not isinstance(t, torch.Tensor) or t.dtype is not dtype or not t.is_cuda:
         raise TypeError("%s must be a CUDA(HIP) tensor of %s" % (name, dtype))
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
@@ -231,12 +243,28 @@ def bnn_conv_output_dims(desc: ConvDesc):
     return tuple(v.value for v in o)
 
 
+def _output_dims(desc: ConvDesc):
+    """bnn_conv_output_dims without the call for ordinary sizes; anything
+    unusual goes through it, for its checks and messages."""
+    H, W, KH, KW, pad, pool = desc.H, desc.W, desc.KH, desc.KW, desc.pad, desc.pool
+    Ho, Wo = H + 2 * pad - KH + 1, W + 2 * pad - KW + 1
+    if (0 < H < 32768 and 0 < W < 32768 and 0 < KH < 128 and 0 < KW < 128 and 0 <= pad < 128
+            and Ho > 1 and Wo > 1 and desc.stride == 1 and 0 < desc.N and 0 < desc.C < 4096
+            and 0 < desc.F < 16384 and desc.N * Ho * Wo < 1 << 24 and desc.N * H * W < 1 << 24
+            and KH * KW * desc.C < 1 << 20):
+        if pool == 2:
+            return Ho, Wo, Ho // 2, Wo // 2
+        if pool == 0:
+            return Ho, Wo, Ho, Wo
+    return bnn_conv_output_dims(desc)
+
+
 def bnn_bconv2d(desc: ConvDesc, x, w, thr=None, flip=None, want_sums=True, want_bits=True,
                 out_sums=None, out_bits=None, stream=None):
     """Binary conv (Eq. 3/4) with fused threshold/flip/OR-pool.  Returns
     (sums [N,Ho,Wo,F] int32 or None, bits [N,Hp,Wp,Fw] int32-storage or None)."""
     lib = load()
-    Ho, Wo, Hp, Wp = bnn_conv_output_dims(desc)
+    Ho, Wo, Hp, Wp = _output_dims(desc)
     _u32(x)
     _u32(w)
     thr = _dev(thr, torch.int32, "thr")
@@ -273,7 +301,7 @@ def bnn_bconv2d_prepared(desc: ConvDesc, x, w, wprep, thr=None, flip=None, want_
                          want_bits=True, out_sums=None, out_bits=None, stream=None):
     """bnn_bconv2d with prepared weights (wprep = bnn_prepare_weights of w)."""
     lib = load()
-    Ho, Wo, Hp, Wp = bnn_conv_output_dims(desc)
+    Ho, Wo, Hp, Wp = _output_dims(desc)
     _u32(x)
     _u32(w)
     _dev(wprep, torch.uint8, "wprep")
@@ -294,7 +322,7 @@ def bnn_fconv2d_binw(desc: ConvDesc, x, w, thr=None, flip=None, want_sums=True,
                      want_bits=True, out_sums=None, out_bits=None, stream=None):
     """fp32-input conv with packed +-1 weights; sums fp32 [N,Ho,Wo,F]."""
     lib = load()
-    Ho, Wo, Hp, Wp = bnn_conv_output_dims(desc)
+    Ho, Wo, Hp, Wp = _output_dims(desc)
     _dev(x, torch.float32, "x")
     _u32(w)
     thr = _dev(thr, torch.int32, "thr")
@@ -330,7 +358,7 @@ def bnn_bconv2d_input(desc: ConvDesc, mode, x, offset, w, thr=None, flip=None, w
     packing).  desc.C is the binarized channel count.  Same outputs as
     bnn_binarize_input / bnn_pack_bits followed by bnn_bconv2d."""
     lib = load()
-    Ho, Wo, Hp, Wp = bnn_conv_output_dims(desc)
+    Ho, Wo, Hp, Wp = _output_dims(desc)
     _dev(x, torch.float32, "x")
     offset = _dev(offset, torch.float32, "offset")
     _u32(w)
@@ -354,7 +382,7 @@ def bnn_fconv_bconv2d(desc0: ConvDesc, desc1: ConvDesc, x, w0, thr0, flip0, w1, 
     layer's packed bits [N, Hp, Wp, F1/32], the same as bnn_fconv2d_binw
     followed by bnn_bconv2d.  w1prep: bnn_prepare_weights of w1, or None."""
     lib = load()
-    _, _, Hp, Wp = bnn_conv_output_dims(desc1)
+    _, _, Hp, Wp = _output_dims(desc1)
     _dev(x, torch.float32, "x")
     _u32(w0)
     _u32(w1)
@@ -379,7 +407,7 @@ def bnn_input_bconv_bconv2d(desc0: ConvDesc, desc1: ConvDesc, mode, x, offset, w
     [N, Hp, Wp, F1/32], the same as bnn_bconv2d_input followed by
     bnn_bconv2d.  w1prep: bnn_prepare_weights of w1, or None."""
     lib = load()
-    _, _, Hp, Wp = bnn_conv_output_dims(desc1)
+    _, _, Hp, Wp = _output_dims(desc1)
     _dev(x, torch.float32, "x")
     offset = _dev(offset, torch.float32, "offset")
     _u32(w0)
@@ -405,7 +433,7 @@ def bnn_bconv_bconv2d(desc0: ConvDesc, desc1: ConvDesc, x, w0, thr0, flip0, w1, 
     chip: returns the second conv's packed bits [N, Hp, Wp, F1/32], the same
     as bnn_bconv2d(desc0) followed by bnn_bconv2d(desc1)."""
     lib = load()
-    _, _, Hp, Wp = bnn_conv_output_dims(desc1)
+    _, _, Hp, Wp = _output_dims(desc1)
     _u32(x)
     _u32(w0)
     _u32(w1)
