@@ -12,6 +12,8 @@
 // sums according to the (wave-uniform) weight bits: one sign flip and one add
 // per multiply-accumulate.
 
+#include <type_traits>
+
 #include "fp32_split.hpp"
 #include "kernels.hpp"
 #include "lane_ops.hpp"
@@ -328,13 +330,18 @@ constexpr int kMfTileW = 32;
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-template <int C, int KH, int KW, bool POOL, bool FULL, int FG>
+constexpr int kSumStride = 68;  // floats per pixel of a 16 x 64 sums tile in LDS
+
+// SUMS: the sums are wanted.
+template <int C, int KH, int KW, bool POOL, bool FULL, int FG, bool SUMS>
 __global__ __launch_bounds__(256) void fconv_mfma_kernel(FconvArgs a) {
   constexpr int K = KH * KW * C;
   constexpr int KC = (K + 31) / 32;  // k-chunks of 32
   constexpr int LW = kMfTileW + KW - 1;
   constexpr int LH = kMfTileH + KH - 1;
-  __shared__ float tile[LH * LW * C];
+  // the staged input's three bf16 parts, and each wave's sums on their way out
+  __shared__ uint16_t tile[3][LH * LW * C];
+  __shared__ __attribute__((aligned(16))) float stg[SUMS ? 4 : 1][SUMS ? 16 * kSumStride : 1];
   __shared__ v8bf wop[FG][KC][4][64];
 
   const int lane = threadIdx.x & 63;
@@ -390,19 +397,36 @@ __global__ __launch_bounds__(256) void fconv_mfma_kernel(FconvArgs a) {
     fll[threadIdx.x] = (a.flip && wi < a.Fw) ? a.flip[wi] : 0u;
   }
 
-  // Stage the input tile (zero outside the image).
-  for (int e = threadIdx.x; e < LH * LW * C; e += 256) {
+  // Stage the input tile (zero outside the image): all loads first (clamped
+  // addresses, no branch), then each value split once into its three parts
+  // (split for every tap that reads it, as before, it was 9 times the work).
+  constexpr int NX = LH * LW * C, XIT = (NX + 255) / 256;
+  float xv[XIT];
+#pragma unroll
+  for (int i = 0; i < XIT; ++i) {
+    const int e = threadIdx.x + 256 * i;
     const int ch = e % C;
     const int t = e / C;
     const int col = t % LW, row = t / LW;
     const int hi = i0 + row - a.pad, wi = j0 + col - a.pad;
-    float v = 0.0f;
-    if (hi >= 0 && hi < a.H && wi >= 0 && wi < a.W)
-      v = a.in[((static_cast<size_t>(n) * a.H + hi) * a.W + wi) * C + ch];
-    tile[e] = v;
+    const bool in = hi >= 0 && hi < a.H && wi >= 0 && wi < a.W;
+    const int hc = min(max(hi, 0), a.H - 1), wc = min(max(wi, 0), a.W - 1);
+    const float v = a.in[((static_cast<size_t>(n) * a.H + hc) * a.W + wc) * C + ch];
+    xv[i] = in ? v : 0.0f;
+  }
+#pragma unroll
+  for (int i = 0; i < XIT; ++i) {
+    const int e = threadIdx.x + 256 * i;
+    if (e < NX) {
+      const Split3 sp = split3(xv[i]);
+      tile[0][e] = bf16_bits(sp.p0);
+      tile[1][e] = bf16_bits(sp.p1);
+      tile[2][e] = bf16_bits(sp.p2);
+    }
   }
 
-  // LDS offset of this lane's 8 k values relative to a pixel's window origin.
+  // LDS offset of this lane's 8 k values relative to a pixel's window origin
+  // (past K: the window's first value, whose weight is 0 there).
   int rel[KC][8];
 #pragma unroll
   for (int kc = 0; kc < KC; ++kc)
@@ -411,7 +435,7 @@ __global__ __launch_bounds__(256) void fconv_mfma_kernel(FconvArgs a) {
       const int k = 32 * kc + 8 * q + e;
       const int tap = k / C, ch = k - (k / C) * C;
       const int kh = tap / KW, kw = tap - (tap / KW) * KW;
-      rel[kc][e] = k < K ? (kh * LW + kw) * C + ch : -1;
+      rel[kc][e] = k < K ? (kh * LW + kw) * C + ch : 0;
     }
   __syncthreads();
 
@@ -434,20 +458,14 @@ __global__ __launch_bounds__(256) void fconv_mfma_kernel(FconvArgs a) {
   for (int tp = 0; tp < 4; ++tp) {
     const int pbase = (pr[tp] * LW + pc[tp]) * C;
 #pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
-      uint16_t p0[8], p1[8], p2[8];
+    for (int kc = 0; kc < KC; ++kc)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float xv = tile[pbase + max(rel[kc][e], 0)];
-        const Split3 sp = split3(rel[kc][e] >= 0 ? xv : 0.0f);
-        p0[e] = bf16_bits(sp.p0);
-        p1[e] = bf16_bits(sp.p1);
-        p2[e] = bf16_bits(sp.p2);
+      for (int pt = 0; pt < 3; ++pt) {
+        uint16_t p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] = tile[pt][pbase + rel[kc][e]];
+        xp[pt][kc][tp] = bf16x8(p);
       }
-      xp[0][kc][tp] = bf16x8(p0);
-      xp[1][kc][tp] = bf16x8(p1);
-      xp[2][kc][tp] = bf16x8(p2);
-    }
   }
 
 #pragma unroll
@@ -476,17 +494,43 @@ __global__ __launch_bounds__(256) void fconv_mfma_kernel(FconvArgs a) {
 
     // Epilogue: lane (q, c) holds pixel c of each tile and filters 16 tf + 4 q + r.
     const int nf = FULL ? 64 : min(64, a.F - f0);
+    if constexpr (SUMS) {
+      // A tile's 16 pixels x 64 sums go through the wave's LDS region, so that
+      // 16 lanes store a pixel's 64 sums as one run of 256 bytes (stored from
+      // the accumulators, an instruction wrote 64 bytes to each of 16 pixels:
+      // 32 images of 112 x 112 x 3 -> 64 with bits 30.9 us, 25.1 here).
+      float* st = stg[wave];
 #pragma unroll
-    for (int tp = 0; tp < 4; ++tp) {
-      const int i = i0 + pr[tp], j = j0 + pc[tp];
-      const bool pix = i < a.Ho && j < a.Wo;
-      if (a.sums && pix) {
-        float* sp = a.sums + (static_cast<size_t>(n * a.Ho + i) * a.Wo + j) * a.F + f0 + 4 * q;
+      for (int tp = 0; tp < 4; ++tp) {
 #pragma unroll
         for (int tf = 0; tf < 4; ++tf)
+          *reinterpret_cast<v4f*>(&st[c * kSumStride + 16 * tf + 4 * q]) = acc[tf][tp];
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (FULL || tf * 16 + 4 * q + r < nf) sp[tf * 16 + r] = acc[tf][tp][r];
+        for (int r = 0; r < 4; ++r) {
+          // lanes 16 r' .. 16 r' + 15: pixel 4 r + r' of the tile
+          const int px = 4 * r + q;
+          int ri, ci;
+          if constexpr (POOL) {
+            const int win = wave * 16 + tp * 4 + (px >> 2);
+            ri = 2 * (win / 16) + ((px >> 1) & 1);
+            ci = 2 * (win % 16) + (px & 1);
+          } else {
+            ri = 2 * wave + (tp >> 1);
+            ci = 16 * (tp & 1) + px;
+          }
+          const int i = i0 + ri, j = j0 + ci;
+          const v4f v = *reinterpret_cast<const v4f*>(&st[px * kSumStride + 4 * c]);
+          if (i < a.Ho && j < a.Wo) {
+            float* sp = a.sums + (static_cast<size_t>(n * a.Ho + i) * a.Wo + j) * a.F + f0 + 4 * c;
+            if (FULL || ((a.F & 3) == 0 && 4 * c < nf)) {
+              *reinterpret_cast<v4f*>(sp) = v;
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (4 * c + e < nf) sp[e] = v[e];
+            }
+          }
+        }
       }
     }
     if (!a.bits) continue;
@@ -498,51 +542,37 @@ __global__ __launch_bounds__(256) void fconv_mfma_kernel(FconvArgs a) {
         const int fl = tf * 16 + 4 * q + r;
         thf[tf][r] = thl[64 * g + fl];
       }
-    const int w0 = f0 / 32;
+    // The sign bit of S - thr is set exactly when S < thr (thr_ceil_f32), the
+    // complement of the output bit: one subtraction and one v_alignbit per
+    // value.  Lane row q holds 8 bits of each of a pixel's two words; three
+    // swaps leave row q with word q % 2 of tile q / 2 of a pair of tiles.
+    const int w0 = f0 / 32, wq = w0 + (q & 1);
+    const uint32_t nfl = ~fll[2 * g + (q & 1)];
+    const uint32_t fm = !FULL && wq == a.Fw - 1 ? tail_mask(a.F) : ~0u;
 #pragma unroll
-    for (int tp = 0; tp < 4; ++tp) {
-      uint32_t word[2] = {0u, 0u};
+    for (int tp = 0; tp < 4; tp += 2) {
+      uint32_t word[2][2] = {{0u, 0u}, {0u, 0u}};
 #pragma unroll
-      for (int tf = 0; tf < 4; ++tf)
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int fl = tf * 16 + 4 * q + r;
-          const bool on = acc[tf][tp][r] >= thf[tf][r] && (FULL || fl < nf);
-          word[tf >> 1] |= static_cast<uint32_t>(on) << (31 - (16 * (tf & 1) + 4 * q + r));
+        for (int tf = 0; tf < 4; ++tf) {
+          uint32_t nib = 0u;
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            nib = __builtin_amdgcn_alignbit(
+                nib, __float_as_uint(acc[tf][tp + t][r] - thf[tf][r]), 31);
+          word[t][tf >> 1] |= nib << (28 - 16 * (tf & 1) - 4 * q);
         }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        word[h] = or_xor32(or_xor16(word[h]));
-        if (FULL || w0 + h < a.Fw) {
-          word[h] ^= fll[2 * g + h];
-          if (!FULL && w0 + h == a.Fw - 1) word[h] &= tail_mask(a.F);
-        }
-        if constexpr (POOL) {
-          word[h] = or_quad(word[h]);
-        }
-      }
-      const int i = i0 + pr[tp], j = j0 + pc[tp];
+      uint32_t w = (or_rows4(word[0][0], word[0][1], word[1][0], word[1][1]) ^ nfl) & fm;
+      if constexpr (POOL) w = or_quad(w);
+      const int i = i0 + (q < 2 ? pr[tp] : pr[tp + 1]), j = j0 + (q < 2 ? pc[tp] : pc[tp + 1]);
       if constexpr (POOL) {
         const int ip = i >> 1, jp = j >> 1;
-        if (q == 0 && (c & 3) == 0 && ip < a.Hp && jp < a.Wp) {
-          uint32_t* op = a.bits + (static_cast<size_t>(n * a.Hp + ip) * a.Wp + jp) * a.Fw + w0;
-          if (FULL)
-            *reinterpret_cast<uint2*>(op) = make_uint2(word[0], word[1]);
-          else {
-            op[0] = word[0];
-            if (w0 + 1 < a.Fw) op[1] = word[1];
-          }
-        }
+        if ((c & 3) == 0 && ip < a.Hp && jp < a.Wp && (FULL || wq < a.Fw))
+          a.bits[(static_cast<size_t>(n * a.Hp + ip) * a.Wp + jp) * a.Fw + wq] = w;
       } else {
-        if (q == 0 && i < a.Ho && j < a.Wo) {
-          uint32_t* op = a.bits + (static_cast<size_t>(n * a.Ho + i) * a.Wo + j) * a.Fw + w0;
-          if (FULL)
-            *reinterpret_cast<uint2*>(op) = make_uint2(word[0], word[1]);
-          else {
-            op[0] = word[0];
-            if (w0 + 1 < a.Fw) op[1] = word[1];
-          }
-        }
+        if (i < a.Ho && j < a.Wo && (FULL || wq < a.Fw))
+          a.bits[(static_cast<size_t>(n * a.Ho + i) * a.Wo + j) * a.Fw + wq] = w;
       }
     }
   }
@@ -584,25 +614,28 @@ hipError_t run_fmfma(const ConvGeom& g, bool pool, const float* in, const uint32
       (g.F >= 128 && static_cast<int64_t>(tiles) * ((g.F + 127) / 128) * 4 >= 4096) ? 2 : 1;
   const bool full = g.F % 64 == 0;
   dim3 grid(tiles, static_cast<unsigned>((g.F + 64 * fg - 1) / (64 * fg)));
-  if (fg == 2) {
-    if (pool && full)
-      fconv_mfma_kernel<C, 3, 3, true, true, 2><<<grid, dim3(256), 0, s>>>(a);
-    else if (pool)
-      fconv_mfma_kernel<C, 3, 3, true, false, 2><<<grid, dim3(256), 0, s>>>(a);
-    else if (full)
-      fconv_mfma_kernel<C, 3, 3, false, true, 2><<<grid, dim3(256), 0, s>>>(a);
+  auto launch = [&](auto fgc, auto pc, auto fc) {
+    constexpr int FG = decltype(fgc)::value;
+    constexpr bool P = decltype(pc)::value, FU = decltype(fc)::value;
+    if (sums)
+      fconv_mfma_kernel<C, 3, 3, P, FU, FG, true><<<grid, dim3(256), 0, s>>>(a);
     else
-      fconv_mfma_kernel<C, 3, 3, false, false, 2><<<grid, dim3(256), 0, s>>>(a);
-  } else {
+      fconv_mfma_kernel<C, 3, 3, P, FU, FG, false><<<grid, dim3(256), 0, s>>>(a);
+  };
+  auto by_shape = [&](auto fgc) {
     if (pool && full)
-      fconv_mfma_kernel<C, 3, 3, true, true, 1><<<grid, dim3(256), 0, s>>>(a);
+      launch(fgc, std::true_type{}, std::true_type{});
     else if (pool)
-      fconv_mfma_kernel<C, 3, 3, true, false, 1><<<grid, dim3(256), 0, s>>>(a);
+      launch(fgc, std::true_type{}, std::false_type{});
     else if (full)
-      fconv_mfma_kernel<C, 3, 3, false, true, 1><<<grid, dim3(256), 0, s>>>(a);
+      launch(fgc, std::false_type{}, std::true_type{});
     else
-      fconv_mfma_kernel<C, 3, 3, false, false, 1><<<grid, dim3(256), 0, s>>>(a);
-  }
+      launch(fgc, std::false_type{}, std::false_type{});
+  };
+  if (fg == 2)
+    by_shape(std::integral_constant<int, 2>{});
+  else
+    by_shape(std::integral_constant<int, 1>{});
   return hipGetLastError();
 }
 
