@@ -11,11 +11,14 @@
 // the end the wave writes those rows out whole: consecutive lanes store
 // consecutive 8-byte pieces of adjacent rows, where storing each word
 // straight from its lane touched 64 rows per instruction, 4 bytes each (the
-// stores then took about 40 % of the kernel).  The block's thresholds (as
+// stores then took about 40 % of the kernel).  Where whole rows per block
+// would leave the last round of blocks nearly empty, a block takes a half, a
+// quarter or an eighth of the filters.  The block's thresholds (as
 // 0.5 - thr, the accumulators' start value) and flip words are staged in LDS
 // once.
 #include <stdint.h>
 
+#include "fastdiv.hpp"
 #include "fp4_expand.hpp"
 #include "kernels.hpp"
 
@@ -23,6 +26,7 @@ namespace bnn {
 namespace {
 
 constexpr int kPix = 256;   // pixels per block: 4 waves x 64
+constexpr int kCUs = 256;   // compute units of the chip
 constexpr int kMaxF = 1024;  // LDS: output rows 34 KB + thresholds 4 KB at F = 1024
 
 struct B1Args {
@@ -32,6 +36,8 @@ struct B1Args {
   const uint32_t* flip;  // [Fw] or null
   uint32_t* bits;        // [M, Fw]
   int32_t M, F, Fw, K;
+  int32_t fpb;           // filters per block
+  FastDiv31 div_g;       // filter groups
 };
 
 // KS consecutive words of a row: one 128-, 64- or 32-bit load.
@@ -61,14 +67,20 @@ __global__ __launch_bounds__(256) void bconv1x1_kernel(B1Args a) {
   constexpr int CW = 2 * KS;
   __shared__ float thl[kMaxF];
   __shared__ uint32_t nfl[kMaxF / 32];
-  // The wave's output rows: 64 rows of Fw words at stride Fw + 2 (8-byte
+  // The wave's output rows: 64 rows of fpb / 32 words at that stride + 2 (8-byte
   // aligned; an odd half-stride spreads a column over the banks).
   extern __shared__ uint32_t ostage[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int h = lane >> 5, c = lane & 31;
-  const int p0 = blockIdx.x * kPix + wave * 64;
-  const int os = a.Fw + 2;
+  // Block b runs on XCD b mod 8; the filter groups of a pixel block follow
+  // each other on one XCD, whose L2 then holds its rows whole.
+  const uint32_t k = blockIdx.x >> 3;
+  const uint32_t pb = fdiv(k, a.div_g);
+  const int fb = static_cast<int>(k - pb * a.div_g.d) * a.fpb;  // first filter
+  const int p0 = static_cast<int>(8 * pb + (blockIdx.x & 7)) * kPix + wave * 64;
+  const int ow = a.fpb / 32;  // words per row of this block
+  const int os = ow + 2;
   uint32_t* orow = ostage + wave * 64 * os;
 
   // Pixel words and the first chunk's weight words, then the thresholds
@@ -84,10 +96,10 @@ __global__ __launch_bounds__(256) void bconv1x1_kernel(B1Args a) {
   uint32_t wa[2][KS], wb[2][KS];
 #pragma unroll
   for (int tf = 0; tf < 2; ++tf)
-    load_words<KS>(a.w + static_cast<size_t>(32 * tf + c) * CW + h * KS, wa[tf]);
-  for (int f = threadIdx.x; f < a.F; f += 256)
-    thl[f] = 0.5f - static_cast<float>(min(max(a.thr[f], -a.K - 1), a.K + 1));
-  for (int i = threadIdx.x; i < a.Fw; i += 256) nfl[i] = ~(a.flip ? a.flip[i] : 0u);
+    load_words<KS>(a.w + static_cast<size_t>(fb + 32 * tf + c) * CW + h * KS, wa[tf]);
+  for (int f = threadIdx.x; f < a.fpb; f += 256)
+    thl[f] = 0.5f - static_cast<float>(min(max(a.thr[fb + f], -a.K - 1), a.K + 1));
+  for (int i = threadIdx.x; i < ow; i += 256) nfl[i] = ~(a.flip ? a.flip[fb / 32 + i] : 0u);
 
   const uint32_t smask = __builtin_amdgcn_readfirstlane(0x88888888u);
   uint32_t vfill;
@@ -103,7 +115,7 @@ __global__ __launch_bounds__(256) void bconv1x1_kernel(B1Args a) {
   // pixel c of tile tp; its sign bit is the complement of the output bit.
   // One v_permlane32_swap of the two filter tiles' words leaves lane half h
   // with the whole word of tile h.
-  const int nch = a.F / 64;
+  const int nch = a.fpb / 64;
   auto chunk = [&](int ch, const uint32_t (&cw)[2][KS], uint32_t (&nw)[2][KS]) {
     const int f0 = 64 * ch;
     v8i A[2][KS];
@@ -112,7 +124,8 @@ __global__ __launch_bounds__(256) void bconv1x1_kernel(B1Args a) {
     if (ch + 1 < nch) {
 #pragma unroll
       for (int tf = 0; tf < 2; ++tf)
-        load_words<KS>(a.w + static_cast<size_t>(f0 + 64 + 32 * tf + c) * CW + h * KS, nw[tf]);
+        load_words<KS>(a.w + static_cast<size_t>(fb + f0 + 64 + 32 * tf + c) * CW + h * KS,
+                       nw[tf]);
     }
     v16f acc[2][2];
 #pragma unroll
@@ -158,17 +171,17 @@ __global__ __launch_bounds__(256) void bconv1x1_kernel(B1Args a) {
   }
   __syncthreads();
 
-  // Rows out: hw = Fw / 2 pieces of 8 bytes per row, rpi whole rows per
+  // Rows out: hw = fpb / 64 pieces of 8 bytes per row, rpi whole rows per
   // store instruction (lanes past rpi * hw idle), rows p0 .. p0 + 63 being
   // adjacent in memory.
-  const int hw = a.Fw / 2;
+  const int hw = ow / 2;
   const int rpi = 64 / hw;
   const int r0 = lane / hw, q = lane - r0 * hw;
   if (r0 < rpi) {
     for (int r = r0; r < 64; r += rpi) {
       if (p0 + r >= a.M) break;
       const uint2 v = *reinterpret_cast<const uint2*>(&orow[r * os + 2 * q]);
-      *reinterpret_cast<uint2*>(&a.bits[static_cast<size_t>(p0 + r) * a.Fw + 2 * q]) = v;
+      *reinterpret_cast<uint2*>(&a.bits[static_cast<size_t>(p0 + r) * a.Fw + fb / 32 + 2 * q]) = v;
     }
   }
 }
@@ -197,8 +210,26 @@ hipError_t launch_bconv1x1(const ConvGeom& g, const uint32_t* in, const uint32_t
   a.F = g.F;
   a.Fw = g.Fw;
   a.K = g.C;
-  const unsigned blocks = static_cast<unsigned>((a.M + kPix - 1) / kPix);
-  const size_t lds = static_cast<size_t>(4 * 64) * (g.Fw + 2) * sizeof(uint32_t);
+  // Filters per block: all of them, or a half, quarter or eighth (at least 4
+  // chunks) where the finer grid's last round is that much fuller, at about 2
+  // % per extra group for the operands built again.  56 x 56 x 256 -> 1024 at
+  // batch 64 is 3.06 whole-row blocks per compute unit, of which some took a
+  // fourth: 34.1 us, 29.6 in quarters.
+  const int64_t pb = (int64_t{a.M} + kPix - 1) / kPix;
+  int groups = 1;
+  double best = 0;
+  for (int s2 = 1; s2 <= 8 && g.F % (64 * s2) == 0 && (s2 == 1 || g.F / s2 >= 256); s2 *= 2) {
+    const double cost =
+        static_cast<double>((pb * s2 + kCUs - 1) / kCUs) / s2 * (1 + 0.02 * (s2 - 1));
+    if (s2 == 1 || cost < best) {
+      best = cost;
+      groups = s2;
+    }
+  }
+  a.fpb = g.F / groups;
+  a.div_g = make_fastdiv31(static_cast<uint32_t>(groups));
+  const unsigned blocks = static_cast<unsigned>((pb + 7) / 8 * 8 * groups);
+  const size_t lds = static_cast<size_t>(4 * 64) * (a.fpb / 32 + 2) * sizeof(uint32_t);
   switch (g.Cw) {
     case 2: bconv1x1_kernel<1><<<blocks, 256, lds, s>>>(a); break;
     case 4: bconv1x1_kernel<2><<<blocks, 256, lds, s>>>(a); break;
