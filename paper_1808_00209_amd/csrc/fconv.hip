@@ -612,7 +612,9 @@ hipError_t run_fmfma(const ConvGeom& g, bool pool, const float* in, const uint32
   // on smaller grids the extra parallelism of one group per block wins.
   const int fg =
       (g.F >= 128 && static_cast<int64_t>(tiles) * ((g.F + 127) / 128) * 4 >= 4096) ? 2 : 1;
-  const bool full = g.F % 64 == 0;
+  // (whole blocks of filters: with two groups per block and an odd number of
+  // groups the last block's second one lies past F and is left out)
+  const bool full = g.F % (64 * fg) == 0;
   dim3 grid(tiles, static_cast<unsigned>((g.F + 64 * fg - 1) / (64 * fg)));
   auto launch = [&](auto fgc, auto pc, auto fc) {
     constexpr int FG = decltype(fgc)::value;

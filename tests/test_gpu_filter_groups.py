@@ -1,0 +1,64 @@
+"""Layers whose filters are split over blocks or groups, where the split can go
+wrong: the real-valued first layer with an odd number of 64-filter groups (two
+to a block on large grids), ragged filter counts beside its contiguous sum
+stores, and 1x1 layers whose blocks take a half or a quarter of the filters.
+The reference is the vector-ALU kernel, itself checked against the oracle; the
+first layer's inputs lie on a 2^-8 grid, so its fp32 sums are exact in any
+order and every sum and word must agree."""
+import pytest
+import torch
+
+from paper_1808_00209_amd import bnn
+
+pytestmark = pytest.mark.gpu
+
+FCONV = [
+    # N, H, W, C, F, pool
+    (32, 64, 64, 3, 192, 0), (32, 64, 64, 1, 320, 2), (32, 62, 63, 3, 160, 2),
+    (32, 64, 64, 3, 128, 0), (3, 23, 45, 3, 70, 0), (2, 17, 33, 1, 36, 2), (1, 9, 31, 3, 192, 2),
+]
+CONV1 = [
+    # N, H, W, C, F: 257 blocks of 256 pixels, the last one partial, or 769
+    (1, 257, 255, 256, 1024), (1, 257, 255, 128, 512), (1, 257, 255, 64, 768),
+    (3, 256, 257, 256, 512), (1, 256, 256, 64, 1024),
+]
+
+
+def _words(g, *shape):
+    return torch.randint(-2 ** 31, 2 ** 31, shape, generator=g, device="cuda",
+                         dtype=torch.int64).to(torch.int32)
+
+
+def _same(call):
+    got = call()
+    with bnn.options(algo=bnn.ALGO_VALU):
+        ref = call()
+    for a, b in zip(got, ref):
+        assert (a is None) == (b is None)
+        if a is not None:
+            assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("case", FCONV, ids=[str(c) for c in FCONV])
+@pytest.mark.parametrize("sums,bits", [(False, True), (True, True), (True, False)])
+def test_first_layer_filter_groups(case, sums, bits):
+    N, H, W, C, F, pool = case
+    g = torch.Generator(device="cuda").manual_seed(H * W + F)
+    x = torch.randint(-1024, 1025, (N, H, W, C), generator=g, device="cuda").float() / 256
+    w = _words(g, F, 3, 3, bnn.words(C))
+    thr = torch.randint(-12, 13, (F,), generator=g, device="cuda").to(torch.int32)
+    flip = _words(g, bnn.words(F))
+    desc = bnn.conv_desc(N, H, W, C, F, 3, 3, 1, 1, pool)
+    _same(lambda: bnn.bnn_fconv2d_binw(desc, x, w, thr, flip, want_sums=sums, want_bits=bits))
+
+
+@pytest.mark.parametrize("case", CONV1, ids=[str(c) for c in CONV1])
+def test_1x1_filter_groups(case):
+    N, H, W, C, F = case
+    g = torch.Generator(device="cuda").manual_seed(H * W + C + F)
+    x, w = _words(g, N, H, W, bnn.words(C)), _words(g, F, 1, 1, bnn.words(C))
+    thr = torch.randint(-20, 21, (F,), generator=g, device="cuda").to(torch.int32)
+    thr[0], thr[-1] = 2 ** 31 - 1, -2 ** 31
+    flip = _words(g, bnn.words(F))
+    desc = bnn.conv_desc(N, H, W, C, F, 1, 1, 1, 0, 0)
+    _same(lambda: bnn.bnn_bconv2d(desc, x, w, thr, flip, want_sums=False))
