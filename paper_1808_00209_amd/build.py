@@ -19,9 +19,9 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libbnn.so")
 BUILD_DIR = os.path.join(PKG, "_build")
 
-SOURCES = ["pack.hip", "bconv_valu.hip", "bconv_mfma.hip", "bconv_tile.hip", "bconv_1x1.hip", "bconv_patch.hip", "fconv.hip",
-           "fconv_bconv.hip", "bconv_bconv.hip", "bfc_chain.hip", "bfc_pair.hip", "bfc_gemm.hip",
-           "bfc_tile.hip",            "api.cpp"]
+SOURCES = ["pack.hip", "bconv_valu.hip", "bconv_mfma.hip", "bconv_tile.hip", "bconv_1x1.hip",
+           "bconv_patch.hip", "fconv.hip", "fconv_bconv.hip", "bconv_bconv.hip", "bfc_chain.hip",
+           "bfc_pair.hip", "bfc_gemm.hip", "bfc_tile.hip", "api.cpp"]
 ARCH = os.environ.get("BNN_OFFLOAD_ARCH", "gfx950")
 
 COMMON = [

@@ -12,10 +12,9 @@
 // consecutive 8-byte pieces of adjacent rows, where storing each word
 // straight from its lane touched 64 rows per instruction, 4 bytes each (the
 // stores then took about 40 % of the kernel).  Where whole rows per block
-// would leave the last round of blocks nearly empty, a block takes a half, a
-// quarter or an eighth of the filters.  The block's thresholds (as
-// 0.5 - thr, the accumulators' start value) and flip words are staged in LDS
-// once.
+// would leave the last round of blocks nearly empty, a block takes a half or a
+// quarter of the filters.  The block's thresholds (as 0.5 - thr, the
+// accumulators' start value) and flip words are staged in LDS once.
 #include <stdint.h>
 
 #include "fastdiv.hpp"
@@ -93,10 +92,13 @@ __global__ __launch_bounds__(256) void bconv1x1_kernel(B1Args a) {
     pv[tp] = p < a.M;
     load_words<KS>(a.in + static_cast<size_t>(pv[tp] ? p : a.M - 1) * CW + h * KS, xw[tp]);
   }
+  // Row 8 g + 4 h' + r of a weight tile (g, r < 4) holds filter 16 h' + 4 g + r:
+  // a lane half's 16 results are then 16 consecutive filters.
+  const int wrow = 16 * ((c >> 2) & 1) + 4 * (c >> 3) + (c & 3);
   uint32_t wa[2][KS], wb[2][KS];
 #pragma unroll
   for (int tf = 0; tf < 2; ++tf)
-    load_words<KS>(a.w + static_cast<size_t>(fb + 32 * tf + c) * CW + h * KS, wa[tf]);
+    load_words<KS>(a.w + static_cast<size_t>(fb + 32 * tf + wrow) * CW + h * KS, wa[tf]);
   for (int f = threadIdx.x; f < a.fpb; f += 256)
     thl[f] = 0.5f - static_cast<float>(min(max(a.thr[fb + f], -a.K - 1), a.K + 1));
   for (int i = threadIdx.x; i < ow; i += 256) nfl[i] = ~(a.flip ? a.flip[fb / 32 + i] : 0u);
@@ -111,10 +113,11 @@ __global__ __launch_bounds__(256) void bconv1x1_kernel(B1Args a) {
 
   // One chunk of 64 filters: expand its weights, prefetch the next chunk's,
   // MFMAs from 0.5 - thr, then the sign bits.  Register e of lane (h, c)
-  // ends as S - thr + 0.5 of filter f0 + 32 tf + 8 (e / 4) + 4 h + e % 4 at
-  // pixel c of tile tp; its sign bit is the complement of the output bit.
-  // One v_permlane32_swap of the two filter tiles' words leaves lane half h
-  // with the whole word of tile h.
+  // ends as S - thr + 0.5 of filter f0 + 32 tf + 16 h + e at pixel c of tile
+  // tp; its sign bit is the complement of the output bit.  16 v_alignbit
+  // collect them (with the filters in row order, nibble by nibble, it took 21
+  // instructions), and one v_permlane32_swap of the two filter tiles' halves
+  // leaves lane half h with both halves of tile h's word.
   const int nch = a.fpb / 64;
   auto chunk = [&](int ch, const uint32_t (&cw)[2][KS], uint32_t (&nw)[2][KS]) {
     const int f0 = 64 * ch;
@@ -124,7 +127,7 @@ __global__ __launch_bounds__(256) void bconv1x1_kernel(B1Args a) {
     if (ch + 1 < nch) {
 #pragma unroll
       for (int tf = 0; tf < 2; ++tf)
-        load_words<KS>(a.w + static_cast<size_t>(fb + f0 + 64 + 32 * tf + c) * CW + h * KS,
+        load_words<KS>(a.w + static_cast<size_t>(fb + f0 + 64 + 32 * tf + wrow) * CW + h * KS,
                        nw[tf]);
     }
     v16f acc[2][2];
@@ -132,7 +135,7 @@ __global__ __launch_bounds__(256) void bconv1x1_kernel(B1Args a) {
     for (int tf = 0; tf < 2; ++tf) {
       v16f t;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) t[e] = thl[f0 + 32 * tf + 8 * (e >> 2) + 4 * h + (e & 3)];
+      for (int e = 0; e < 16; ++e) t[e] = thl[f0 + 32 * tf + 16 * h + e];
       acc[tf][0] = t;
       acc[tf][1] = t;
     }
@@ -152,16 +155,11 @@ __global__ __launch_bounds__(256) void bconv1x1_kernel(B1Args a) {
       for (int tf = 0; tf < 2; ++tf) {
         wd[tf] = 0u;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          uint32_t nib = 0u;
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            nib = __builtin_amdgcn_alignbit(nib, __float_as_uint(acc[tf][tp][4 * g + r]), 31);
-          wd[tf] |= nib << (28 - 8 * g - 4 * h);
-        }
+        for (int e = 0; e < 16; ++e)
+          wd[tf] = __builtin_amdgcn_alignbit(wd[tf], __float_as_uint(acc[tf][tp][e]), 31);
       }
       const auto sw = __builtin_amdgcn_permlane32_swap(wd[0], wd[1], false, false);
-      orow[(32 * tp + c) * os + f0 / 32 + h] = (sw[0] | sw[1]) ^ fx;
+      orow[(32 * tp + c) * os + f0 / 32 + h] = ((sw[0] << 16) | sw[1]) ^ fx;
     }
   };
   // Two chunks per trip, so the two weight register sets keep fixed names.
@@ -210,15 +208,15 @@ hipError_t launch_bconv1x1(const ConvGeom& g, const uint32_t* in, const uint32_t
   a.F = g.F;
   a.Fw = g.Fw;
   a.K = g.C;
-  // Filters per block: all of them, or a half, quarter or eighth (at least 4
-  // chunks) where the finer grid's last round is that much fuller, at about 2
-  // % per extra group for the operands built again.  56 x 56 x 256 -> 1024 at
+  // Filters per block: all of them, or a half or quarter (at least 4 chunks)
+  // where the finer grid's last round is that much fuller, at about 2 % per
+  // extra group for the operands built again.  56 x 56 x 256 -> 1024 at
   // batch 64 is 3.06 whole-row blocks per compute unit, of which some took a
   // fourth: 34.1 us, 29.6 in quarters.
   const int64_t pb = (int64_t{a.M} + kPix - 1) / kPix;
   int groups = 1;
   double best = 0;
-  for (int s2 = 1; s2 <= 8 && g.F % (64 * s2) == 0 && (s2 == 1 || g.F / s2 >= 256); s2 *= 2) {
+  for (int s2 = 1; s2 <= 4 && g.F % (64 * s2) == 0 && (s2 == 1 || g.F / s2 >= 256); s2 *= 2) {
     const double cost =
         static_cast<double>((pb * s2 + kCUs - 1) / kCUs) / s2 * (1 + 0.02 * (s2 - 1));
     if (s2 == 1 || cost < best) {
