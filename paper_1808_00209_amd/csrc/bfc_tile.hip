@@ -5,9 +5,9 @@
 // The FC kernel (bfc_gemm.hip) gives each wave one 32 x 32 tile and expands
 // both of its operands: 11 vector instructions at 4 cycles each and two LDS
 // reads for every MFMA of 32 cycles.  Here a workgroup of 4 waves computes up
-// to 256 outputs x 128 rows, a wave 64 outputs x 32 PT rows: per k-step two weight
-// operands (expanded in registers from packed words) and PT data operands
-// serve 2 PT MFMAs.  The data rows are staged in LDS, expanded once per
+// to 256 outputs x 128 rows, a wave 64 outputs x 32 PT rows: per k-step two
+// weight operands (expanded in registers from packed words) and PT data
+// operands serve 2 PT MFMAs.  The data rows are staged in LDS, expanded once per
 // workgroup, 256 bits of each at a time in two buffers: while one chunk's
 // MFMAs run, the next one's words (loaded a chunk earlier) are expanded into
 // the other, a few vector instructions after each MFMA (up to 4 hide behind
@@ -15,7 +15,7 @@
 // unit, so that one's MFMAs cover the other's barriers (one of 8 waves: 61
 // against 57 us).  Words and bits past K are staged as fp4 0.0, so their
 // products vanish whatever the weight words hold there.
-// 4096 x 8192 -> 4096, bits: 149 us in the FC kernel, 57 us here (4.8e15
+// 4096 x 8192 -> 4096, bits: 133 us in the FC kernel, 50 us here (5.5e15
 // operations a second; the matrix cores are busy 86 % of the waves' cycles,
 // at a clock that drops to about 1.5 GHz).
 #include <algorithm>

@@ -160,9 +160,9 @@ hipError_t launch_bfc_gemm(int64_t M, int64_t N, int64_t K, const uint32_t* A,
                            int32_t* sums, uint32_t* bits, hipStream_t s);
 
 // Binary FC layer / GEMM at many rows (bfc_tile.hip): up to 256 outputs x
-// 128 rows per workgroup, the data rows staged in LDS as fp4 operands.  Returns false,
-// with nothing launched, for shapes the other kernels are the faster for;
-// otherwise launches and sets *err.
+// 128 rows per workgroup, the data rows staged in LDS as fp4 operands.
+// Returns false, with nothing launched, for shapes the other kernels are the
+// faster for; otherwise launches and sets *err.
 bool launch_bfc_tile(int64_t M, int64_t N, int64_t K, const uint32_t* A, const uint32_t* B,
                      const int32_t* thr, const uint32_t* flip, int32_t* sums, uint32_t* bits,
                      hipStream_t s, hipError_t* err);
