@@ -44,7 +44,7 @@ namespace {
 constexpr uint32_t kOutOfRange = 0x80000000u;  // raw buffer loads read 0 there
 constexpr int kRsrcWord3 = 0x00020000;
 constexpr int kNT = 256;
-constexpr int kSumStride = 36;  // LDS words per pixel of a sums tile (16-byte aligned, odd in 16s)
+constexpr int kSumStride = 68;  // LDS words per pixel of a wave's 64 sums (16-byte aligned, odd in 16s)
 
 struct TileArgs {
   const uint32_t* in;
@@ -402,43 +402,50 @@ __global__ __launch_bounds__(kNT, 2) void bconv_tile_kernel(TileArgs a) {
     }
 
     if constexpr (SUMS) {
-      // A wave's 32 x 32 tile goes through LDS (all waves must be done
-      // with the staged tile) so that a pixel's 32 sums are stored as
-      // one contiguous run (8 lanes x 16 bytes).
+      // A wave's 64 x 32 sums go through LDS (all waves must be done with the
+      // staged tile) so that a pixel's are stored as two contiguous runs (8
+      // lanes x 16 bytes each), its position decoded once for both (a pass per
+      // 32 filters: 50 x 50 x 160 -> 200 pooled at batch 7 13.8 us, 12.8 here; 56 x
+      // 56 x 256 -> 256 at batch 64 73.1, 70.0).
       __syncthreads();
       constexpr int TS = kSumStride;
       int32_t* ts = reinterpret_cast<int32_t*>(act) + wave * (32 * TS);
+      const int f = f0 + 4 * (lane & 7);
 #pragma unroll
-      for (int pt = 0; pt < PT; ++pt)
+      for (int pt = 0; pt < PT; ++pt) {
 #pragma unroll
-        for (int tf = 0; tf < 2; ++tf) {
+        for (int tf = 0; tf < 2; ++tf)
 #pragma unroll
           for (int g = 0; g < 4; ++g)
-            *reinterpret_cast<int4*>(&ts[c * TS + 8 * g + 4 * h]) =
+            *reinterpret_cast<int4*>(&ts[c * TS + 32 * tf + 8 * g + 4 * h]) =
                 int4{static_cast<int>(acc[tf][pt][4 * g]), static_cast<int>(acc[tf][pt][4 * g + 1]),
                      static_cast<int>(acc[tf][pt][4 * g + 2]),
                      static_cast<int>(acc[tf][pt][4 * g + 3])};
-          const int f = f0 + 32 * tf + 4 * (lane & 7);
-#pragma unroll 1
-          for (int r = 0; r < 4; ++r) {
-            const int prow = 8 * r + (lane >> 3);
-            const int item = p0 + (pt * wp + wpi) * 32 + prow;
-            const Pix p = decode(a, min(item, a.items - 1));
-            const int4 v = *reinterpret_cast<const int4*>(&ts[prow * TS + 4 * (lane & 7)]);
-            const int j = p.j + rs * js0;
-            if (item < a.items && p.i < a.Ho && j < a.Wo) {
-              int32_t* dst = a.sums + (static_cast<size_t>(p.n * a.Ho + p.i) * a.Wo + j) * a.F + f;
+#pragma unroll 2
+        for (int r = 0; r < 4; ++r) {
+          const int prow = 8 * r + (lane >> 3);
+          const int item = p0 + (pt * wp + wpi) * 32 + prow;
+          const Pix p = decode(a, min(item, a.items - 1));
+          const int j = p.j + rs * js0;
+          int32_t* dst = a.sums + (static_cast<size_t>(p.n * a.Ho + p.i) * a.Wo + j) * a.F + f;
+          const int4 v[2] = {*reinterpret_cast<const int4*>(&ts[prow * TS + 4 * (lane & 7)]),
+                             *reinterpret_cast<const int4*>(&ts[prow * TS + 32 + 4 * (lane & 7)])};
+          if (item < a.items && p.i < a.Ho && j < a.Wo) {
+#pragma unroll
+            for (int tf = 0; tf < 2; ++tf) {
+              const int ft = f + 32 * tf;
               if ((a.F & 3) == 0) {
-                if (f < a.F) *reinterpret_cast<int4*>(dst) = v;
+                if (ft < a.F) *reinterpret_cast<int4*>(dst + 32 * tf) = v[tf];
               } else {
-                if (f < a.F) dst[0] = v.x;
-                if (f + 1 < a.F) dst[1] = v.y;
-                if (f + 2 < a.F) dst[2] = v.z;
-                if (f + 3 < a.F) dst[3] = v.w;
+                if (ft < a.F) dst[32 * tf] = v[tf].x;
+                if (ft + 1 < a.F) dst[32 * tf + 1] = v[tf].y;
+                if (ft + 2 < a.F) dst[32 * tf + 2] = v[tf].z;
+                if (ft + 3 < a.F) dst[32 * tf + 3] = v[tf].w;
               }
             }
           }
         }
+      }
     }
     if (!SUMS || a.bits) {
       if constexpr (SUMS) add_thresholds();
