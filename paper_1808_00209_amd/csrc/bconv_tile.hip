@@ -37,6 +37,7 @@
 #include "fp4_expand.hpp"
 #include "kernels.hpp"
 #include "lane_ops.hpp"
+#include "tile_plans.hpp"
 
 namespace bnn {
 namespace {
@@ -44,7 +45,6 @@ namespace {
 constexpr uint32_t kOutOfRange = 0x80000000u;  // raw buffer loads read 0 there
 constexpr int kRsrcWord3 = 0x00020000;
 constexpr int kNT = 256;
-constexpr int kSumStride = 68;  // LDS words per pixel of a wave's 64 sums (16-byte aligned, odd in 16s)
 
 struct TileArgs {
   const uint32_t* in;
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(kNT, 2) void bconv_tile_kernel(TileArgs a) {
       // 32 filters: 50 x 50 x 160 -> 200 pooled at batch 7 13.8 us, 12.8 here; 56 x
       // 56 x 256 -> 256 at batch 64 73.1, 70.0).
       __syncthreads();
-      constexpr int TS = kSumStride;
+      constexpr int TS = kConvTileSumStride;
       int32_t* ts = reinterpret_cast<int32_t*>(act) + wave * (32 * TS);
       const int f = f0 + 4 * (lane & 7);
 #pragma unroll
@@ -486,100 +486,6 @@ __global__ __launch_bounds__(kNT, 2) void bconv_tile_kernel(TileArgs a) {
   }
 }
 
-// Launch plan: k-steps per tap and chunk (ks), chunks, pixel tiles per wave
-// (pt), log2 of the waves along the filters (wfl), LDS bytes; ok when the
-// kernel takes the shape.
-struct TilePlan {
-  bool ok;
-  double cost;
-  int ks, nchunk, wfl, RS, Ws, cols;
-  int64_t strips, items, units, fgs;  // units: of 32 pixels per wave, all strips
-  size_t lds;
-  int64_t ups, shares;  // units per strip; shares the units are dealt to
-  int32_t H, W, N, Ho, Wo, Hw, Ww;
-};
-
-// Smallest grids worth it, in units times filter groups (plan_pays).
-constexpr int64_t kUnits = 2048, kTailUnits = 256;
-constexpr size_t kLdsBlock = 79 * 1024;  // dynamic LDS per block: two blocks per CU
-
-TilePlan plan_tile(const ConvGeom& g, bool sums) {
-  TilePlan p = {};
-  const bool pool = g.pool == 2;
-  // A 1x1 conv has no neighbours: its pixels are rows of one column, so that
-  // a block stages only its own pixels.
-  const bool flat = g.KH == 1 && g.KW == 1 && g.pad == 0 && !pool;
-  p.N = flat ? 1 : g.N;
-  p.H = flat ? g.N * g.H * g.W : g.H;
-  p.W = flat ? 1 : g.W;
-  p.Ho = flat ? p.H : g.Ho;
-  p.Wo = flat ? 1 : g.Wo;
-  // pooling windows: whole ones, or with sums wanted also those cut by an
-  // odd edge, so that every pixel is covered
-  p.Hw = pool ? (sums ? (p.Ho + 1) / 2 : p.Ho / 2) : p.Ho;
-  p.Ww = pool ? (sums ? (p.Wo + 1) / 2 : p.Wo / 2) : p.Wo;
-  const int64_t Hv = int64_t{p.H} + 2 * g.pad, rh = pool ? 2 : 1;
-  // Waves along the filters (4, 2 or 1, the rest along the pixels), channel
-  // chunk and strip width: the cheapest in estimated cycles.  Per full run and
-  // wave: its MFMAs (32 cycles, 1.25 times that with the loop's other work),
-  // the staging's vector instructions (about 30 + 8 ks per word half, 4 cycles
-  // each) and about 4500 cycles of start, barriers and epilogue; times the
-  // runs, padded filters and columns included.
-  for (int wfl = 2; wfl >= 0; --wfl) {
-    const int64_t fgs = (g.F + (64 << wfl) - 1) / (64 << wfl);
-    const int64_t unit = (4 >> wfl) * 32, bp = 4 * unit;
-    bool fits = false;
-    // Chunks of at most 8 words, smaller ones where the staged rows do not fit.
-    for (int nch = (g.Cw + 7) / 8; !fits && nch <= g.Cw; ++nch) {
-      const int ks = (g.Cw + 2 * nch - 1) / (2 * nch);
-      const int nchunk = (g.Cw + 2 * ks - 1) / (2 * ks);
-      const int64_t ps = 2 * ks + 1;
-      const double mfma = 1.25 * 32 * 2 * 4 * g.KH * g.KW * ks;
-      for (int64_t S = 1; S <= p.Ww && (S == 1 || p.Ww / S >= 4); ++S) {
-        const int64_t Ws = (p.Ww + S - 1) / S;
-        if (S > 1 && (p.Ww + Ws - 1) / Ws != S) continue;
-        // Virtual rows a run may touch: item rows spanned, the window height,
-        // and the rows skipped at each image boundary crossed.
-        const int64_t per = bp / (rh * rh);
-        const int64_t span = 1 + (per - 1 + Ws - 1) / Ws;
-        const int64_t cross = (span - 1 + p.Hw - 1) / p.Hw;
-        const int64_t skip = Hv - rh * p.Hw > 0 ? Hv - rh * p.Hw : 0;
-        const int64_t rows = rh * span + g.KH - 1 + cross * skip;
-        const int64_t cols = rh * Ws + g.KW - 1;
-        int64_t RS = cols * ps;
-        // Pooled tiles: a row stride of 4 mod 8 entries puts the two rows of a
-        // window on different banks.
-        if (pool) RS += ((4 - RS % 8) + 8) % 8;
-        size_t lds = static_cast<size_t>(rows * RS) * 16;
-        if (sums && lds < 4 * 32 * kSumStride * 4) lds = 4 * 32 * kSumStride * 4;
-        if (lds > kLdsBlock) continue;
-        fits = true;
-        const int64_t items = rh * rh * int64_t{p.N} * p.Hw * Ws;
-        const int64_t ups = (items + unit - 1) / unit;
-        const double cost = static_cast<double>(fgs * S * ups) / 4 *
-                            (nchunk * (mfma + rows * cols / 128.0 * (30 + 8 * ks) * 4) + 4500);
-        if (p.ok && cost >= p.cost) continue;
-        p.ok = true;
-        p.cost = cost;
-        p.wfl = wfl;
-        p.fgs = fgs;
-        p.ks = ks;
-        p.nchunk = nchunk;
-        p.Ws = static_cast<int>(Ws);
-        p.strips = S;
-        p.RS = static_cast<int>(RS);
-        p.lds = lds;
-        p.cols = static_cast<int>(cols);
-        p.items = items;
-        p.ups = ups;
-        p.units = S * ups;
-      }
-      if (ks == 1) break;
-    }
-  }
-  return p;
-}
-
 template <int KS>
 void launch_ks(const TileArgs& a, bool tail, unsigned grid, size_t lds, hipStream_t s) {
   if (a.sums && tail)
@@ -592,46 +498,16 @@ void launch_ks(const TileArgs& a, bool tail, unsigned grid, size_t lds, hipStrea
     bconv_tile_kernel<KS, false, false><<<grid, kNT, lds, s>>>(a);
 }
 
-// Where this kernel is the faster one (graph-timed against the general kernel
-// over 140 random shapes, 2 to 250 images, 32 to 512 channels and filters, 1x1
-// to 5x5).
-bool plan_pays(const ConvGeom& g, const TilePlan& p) {
-  if (!p.ok || p.fgs > 64) return false;
-  // C not a multiple of 64: the general kernel loads word by word and pads in
-  // its loop (x1.04 to x2.4 here from 256 units on; 160 -> 256, 5x5 at 19 x 64
-  // x 64: 108 -> 47 us).
-  if (g.C % 64 != 0) return p.units * p.fgs >= kTailUnits;
-  // Otherwise: a neighbourhood to stage for, one channel chunk (two halve the
-  // work per staging: 512 -> 512 at 28 x 28 x 34 ran 8 % slower here), at
-  // least 9 k-steps per run's pixel (18 when pooling: 64 -> 256 pooled 3 %
-  // slower, 64 -> 128 without pooling 9 % faster), at least two waves along
-  // the filters of which at most 1/8 is padding, and a full run for every
-  // block slot (smaller grids are faster with the general kernel's K split).
-  const int steps = g.KH * g.KW * p.ks;
-  return p.nchunk == 1 && steps >= (g.pool == 2 ? 18 : 9) && p.wfl >= 1 &&
-         8 * p.fgs * (64 << p.wfl) <= 9 * int64_t{g.F} && p.units * p.fgs >= kUnits;
-}
-
 }  // namespace
 
 bool launch_bconv_tile(const ConvGeom& g, const uint32_t* in, const uint32_t* w,
                        const int32_t* thr, const uint32_t* flip, int32_t* sums, uint32_t* bits,
                        hipStream_t s, hipError_t* err) {
-  // What can be told without a plan (a plan takes a few microseconds, which
-  // only large launches hide).  (The options pick variants of the general
-  // kernel; with 32 filters half of every wave's would be padding; a 1x1 conv
-  // has nothing to stage for unless its rows are ragged, and it lost there
-  // too when pooled (96 -> 192 at 64 x 64 x 120: 26 -> 31 us) or of several
-  // chunks (4100 -> 1000 at 4096 rows: 22 -> 44 us).)
+  // The options pick variants of the general kernel.
   const bnn_options& o = options();
   if (o.xcd_order != 1 || o.lds_weights != -1 || o.late_thresholds != -1) return false;
-  const bool ragged = g.C % 64 != 0, one = g.KH * g.KW == 1;
-  if (g.F <= 32 || (one && (!ragged || g.pool == 2)) || ((!ragged || one) && g.Cw > 8)) return false;
-  // (units x filter groups, padding aside, are the outputs / 8192)
-  const int64_t outputs = int64_t{g.N} * (g.Ho + 1) * (g.Wo + 1) * ((g.F + 63) / 64 * 64);
-  if (outputs / 8192 < (ragged ? kTailUnits : kUnits) * 2 / 3) return false;
-  const TilePlan p = plan_tile(g, sums != nullptr);
-  if (!plan_pays(g, p)) return false;
+  ConvTilePlan p;
+  if (!conv_tile_plan(g, sums != nullptr, &p)) return false;
   TileArgs a;
   a.in = in;
   a.w = w;

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "bnn.h"
+#include "conv_geom.hpp"
 
 namespace bnn {
 
@@ -21,12 +22,6 @@ inline __host__ __device__ uint32_t tail_mask(int64_t bits) {
 }
 
 inline int64_t words_of(int64_t bits) { return (bits + 31) >> 5; }
-
-// Geometry of one binary conv launch (stride 1).
-struct ConvGeom {
-  int32_t N, H, W, C, F, KH, KW, pad, pool;
-  int32_t Cw, Fw, Ho, Wo, Hp, Wp;
-};
 
 hipError_t launch_pack_bits(const float* x, const float* offset, int64_t rows,
                             int64_t D, uint32_t* out, hipStream_t s);

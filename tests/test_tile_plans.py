@@ -1,0 +1,82 @@
+"""The plan of the staged-tile conv, on the host: its cost does not grow with
+the map, and no run of it reads or stages outside the LDS tile, for any window
+(square or not), pooled or not, with and without sums (CPU only)."""
+import random
+
+import numpy as np
+import pytest
+
+import tile_plans
+
+
+@pytest.mark.parametrize("W", [1024, 8192, 65536, 262144])
+@pytest.mark.parametrize("C,k,pool", [(96, 3, 0), (128, 3, 2), (1000, 5, 0)])
+def test_plan_costs_the_same_on_wide_maps(W, C, k, pool):
+    # (a step per strip count took 10 times as long at 1024 columns and 1700
+    # times at 262144; the bound leaves room for a busy host)
+    small = tile_plans.conv_tile_host_us((1024 * 1024 // 56 // 56, 56, 56, C, 128, k, k, 1, pool), 0)
+    wide = tile_plans.conv_tile_host_us((max(1, 1024 * 1024 // 8 // W), 8, W, C, 128, k, k, 1, pool), 0)
+    assert wide < 6 * small + 1, (wide, small)
+
+
+def _shapes():
+    rng = random.Random(7)
+    out = [(7, 45, 61, 160, 200, 3, 3, 1, 2), (3, 9, 1500, 96, 64, 3, 3, 1, 0),
+           (5, 7, 9, 64, 128, 1, 4, 0, 2), (2, 1, 70, 96, 64, 1, 3, 1, 0)]
+    while len(out) < 400:
+        KH, KW = rng.randint(1, 6), rng.randint(1, 5)
+        H, W = rng.randint(1, 40), rng.choice([rng.randint(1, 40), rng.randint(41, 400)])
+        s = (rng.randint(1, 9), H, W, rng.choice([32, 64, 100, 256, rng.randint(33, 700)]),
+             rng.randint(33, 300), KH, KW, rng.randint(0, 2), rng.choice([0, 2]))
+        if H + 2 * s[7] - KH >= 1 and W + 2 * s[7] - KW >= 1:
+            out.append(s)
+    return out
+
+
+def _item(p, pool, item):
+    """Image, grid row and output row / column (from the strip's first) of items."""
+    w = item // 4 if pool else item
+    t, jw = w // p["Ws"], w % p["Ws"]
+    n, iw = t // p["Hw"], t % p["Hw"]
+    return (n, iw, 2 * iw + item // 2 % 2, 2 * jw + item % 2) if pool else (n, iw, iw, jw)
+
+
+@pytest.mark.parametrize("sums", [False, True])
+def test_runs_stay_inside_their_lds_tile(sums):
+    """Every run of 1 to 4 units a block may take: the staged rows fit the LDS
+    the plan asks for, and every window of every pixel lies in the staged rows
+    and columns; the strips cover each output pixel once."""
+    planned = 0
+    for shape in _shapes():
+        p = tile_plans.cheapest(shape, sums)
+        if not p["ok"]:
+            continue
+        planned += 1
+        N, H, W, C, F, KH, KW, pad, pool = shape
+        pool = pool == 2
+        rs, wp = (2 if pool else 1), 4 >> p["wfl"]
+        Hv, ps, unit = p["H"] + 2 * pad, 2 * p["ks"] + 1, 32 * (4 >> p["wfl"])
+        assert p["lds"] <= 79 * 1024 and p["cols"] == rs * p["Ws"] + KW - 1
+        assert p["RS"] >= p["cols"] * ps and p["ups"] * unit >= p["items"]
+        n, iw, i, j = _item(p, pool, np.arange(p["items"]))
+        for u in range(p["ups"]):
+            for units in range(1, min(4, p["ups"] - u) + 1):
+                a, b = u * unit, min((u + units) * unit, p["items"])
+                if a >= p["items"]:
+                    continue
+                v0 = n[a] * Hv + rs * iw[a]
+                rows = n[b - 1] * Hv + rs * iw[b - 1] + rs - 1 - v0 + KH
+                assert ((rows - 1) * p["RS"] + p["cols"] * ps) * 16 <= p["lds"], (shape, u, units)
+                r = n[a:b] * Hv + i[a:b] - v0
+                assert r.min() >= 0 and r.max() + KH <= rows, (shape, u, units)
+        assert j.max() + KW <= p["cols"]
+        # coverage: strip s, column js0 + j; pixels outside the map are dropped
+        seen = np.zeros((p["N"], p["Ho"], p["Wo"]), int)
+        for s in range(p["strips"]):
+            col = j + rs * s * p["Ws"]
+            ok = (i < p["Ho"]) & (col < p["Wo"])
+            np.add.at(seen, (n[ok], i[ok], col[ok]), 1)
+        cut = seen if sums or not pool else seen[:, :p["Ho"] // 2 * 2, :p["Wo"] // 2 * 2]
+        assert cut.min() == 1 and seen.max() == 1, shape
+        assert wp * 32 == unit
+    assert planned > 300
