@@ -76,12 +76,13 @@ hipError_t launch_conv(const bnn::ConvGeom& g, const uint32_t* in, const uint32_
     return bnn::launch_bconv1x1(g, in, w, thr, flip, bits, s);
   if (use_mfma(g) && bits && !sums && bnn::bconv_img8_supported(g))
     return bnn::launch_bconv_img8(g, in, w, thr, flip, bits, s);
-  hipError_t err = hipSuccess;
-  if (use_mfma(g) && bnn::launch_bconv_tile(g, in, w, thr, flip, sums, bits, s, &err)) return err;
-  if (use_mfma(g))
-    return bnn::launch_bconv_mfma(g, in, w, wprep && bnn::bconv_mfma_prep_supported(g) ? wprep
-                                                                                         : nullptr,
-                                  thr, flip, sums, bits, s);
+  if (use_mfma(g)) {
+    if (wprep && !bnn::bconv_mfma_prep_supported(g)) wprep = nullptr;
+    hipError_t err = hipSuccess;
+    if (bnn::launch_bconv_tile(g, in, w, thr, flip, sums, bits, wprep != nullptr, s, &err))
+      return err;
+    return bnn::launch_bconv_mfma(g, in, w, wprep, thr, flip, sums, bits, s);
+  }
   return bnn::launch_bconv_valu(g, in, w, thr, flip, sums, bits, s);
 }
 

@@ -29,6 +29,7 @@
 #include "fp4_expand.hpp"
 #include "kernels.hpp"
 #include "lane_ops.hpp"
+#include "tile_plans.hpp"
 
 namespace bnn {
 namespace {
@@ -888,107 +889,13 @@ hipError_t launch_vw(Mfma32Args a, int tf, int ks, bool lds, bool late, bool tai
   return launch32<VW, POOL, false>(a, tf, ks, lds, late, tail, s);
 }
 
-// Launch plan of the matrix-core conv for a geometry: words per lane and
-// iteration (vw), filter tiles per wave (tf), K split (ks), weights through
-// LDS (lds), late threshold staging (late), C not a multiple of 64 (tail),
-// and whether prepared weights pay (prep).
-struct Plan {
-  int vw, tf, ks;
-  bool lds, late, tail, short8, prep;
-};
-
-Plan plan_mfma(const ConvGeom& g, bool pool) {
-  const bnn_options& opt = options();
-  Plan p;
-  const int64_t items = pool ? 4 * int64_t{g.N} * g.Hp * g.Wp : int64_t{g.N} * g.Ho * g.Wo;
-  const int64_t groups = (items + 63) / 64;
-  const int64_t ftiles = (g.F + 31) / 32;
-  // Words per lane, row and iteration: 8-word chunks (128-bit loads) where
-  // the channels allow, which halves the vector-memory instructions per MFMA
-  // (the texture-address unit is the busiest unit of the small grids), but
-  // not when that leaves fewer than 8 iterations to split.
-  // C not a multiple of 64: the loop walks Cc >= Cw words per tap, whole
-  // chunks of 2 VW words, with the words past Cw zeroed and every word
-  // loaded on its own (bconv_mfma32_kernel, TAIL).  VW is the largest of 4,
-  // 2, 1 whose padding stays within 1/8 of the row.
-  p.tail = g.C % 64 != 0;
-  int vw = g.Cw % 8 == 0 ? 4 : g.Cw % 4 == 0 ? 2 : 1;
-  // Windows of at most 4 eight-word chunks (K <= 1024 bits, e.g. FC layers
-  // of 1024 inputs) on grids too small to fill the chip keep 8-word chunks
-  // and no K split: there the split's LDS reduction costs more than it
-  // hides (1024 -> 1024 and 1024 -> 10 at 64 rows: 4.15 and 4.30 us against
-  // 4.42 and 4.57 us with 2-word chunks split 4 ways).
-  const int chunks8 = g.KH * g.KW * (g.Cw / 8);
-  p.short8 = !p.tail && vw == 4 && chunks8 <= 4 && groups * ftiles < 1024;
-  if (vw == 4 && chunks8 < 8 && !p.short8) vw = 2;
-  // Option lds_weights = 1 asks for the LDS-weights kernel wherever no K
-  // split is used; it takes chunks of at most 2 words.
-  if (opt.lds_weights == 1 && vw == 4) vw = 2;
-  if (p.tail) {
-    vw = 1;
-    for (int t = 4; t >= 2 && vw == 1; t /= 2)
-      if (((g.Cw + 2 * t - 1) / (2 * t) * (2 * t) - g.Cw) * 8 <= g.Cw) vw = t;
-  }
-  p.vw = vw;
-  const int Cc = (g.Cw + 2 * vw - 1) / (2 * vw) * (2 * vw);
-  const int iters = g.KH * g.KW * (Cc / (2 * vw));
-
-  // Tile shape and K split: 64-filter wave tiles down to ~1 wave per SIMD
-  // (1024 waves), then 32-filter tiles with a K split over up to 4 waves
-  // until there are ~1 (8-word chunks) or ~2 (smaller chunks) waves per
-  // SIMD, keeping at least 2 iterations per wave.  Splitting 8 ways never
-  // beat 4 (the LDS reduction then costs more than it hides).  With 2-word
-  // chunks, grids of >= 4096 64-filter tiles stage the weights through LDS
-  // (5-20 % faster there, slower on smaller grids); 8-word chunks without
-  // staging were as fast or faster wherever the channels allow them.  All
-  // measured on every layer shape of the networks here.
-  int tf = 2, ks = 1;
-  if (g.F % 64 != 0 || groups * (g.F / 64) < 1024) {
-    tf = 1;
-    const int64_t target = vw == 4 ? 1024 : 2048;
-    while (!p.short8 && ks < 4 && groups * ftiles * ks < target && iters >= 4 * ks) ks *= 2;
-  }
-  bool lds = opt.lds_weights == -1 ? vw <= 2 && tf == 2 && groups * (g.F / 64) >= 4096
-                                    : opt.lds_weights == 1;
-  if (ks > 1 || vw == 4) lds = false;
-  if (p.tail) {
-    tf = 1;
-    lds = false;
-    if (ks > 4) ks = 4;
-  }
-  p.tf = tf;
-  p.ks = ks;
-  p.lds = lds;
-  // Thresholds staged after the main loop on grids of at most 2 waves per
-  // SIMD (2048 waves) with 32-filter tiles, at kernel start otherwise, where
-  // the accumulators can then start from them (16x16x128 -> 256 and
-  // 16x16x256 -> 256 pool at batch 64: 5.98 / 7.50 us early against
-  // 6.25 / 7.94 us late; 8x8x256 -> 512 with 32-filter tiles: 6.11 us late,
-  // 6.22 us early).  Option late_thresholds overrides.
-  const int64_t waves = (groups + 3) / 4 * 4 * ((g.F + 32 * tf - 1) / (32 * tf));
-  p.late = p.tail || (opt.late_thresholds == -1 ? waves <= 2048 && tf == 1
-                                                 : opt.late_thresholds == 1);
-  // Prepared weights where they pay (graph-timed on every conv shape of the
-  // networks here): 32-filter tiles, where a wave's vector-ALU work per MFMA
-  // then drops from 12 to 8 instructions (8x8x512 -> 512 pool at batch 64:
-  // 9.7 -> 8.2 us; 8x8x256 -> 512: 6.6 -> 6.0 us), and rows of at most 2
-  // words.  With 64-filter tiles over 256 or more channels the prepared
-  // operands' registers cost a wave per SIMD (180 against 154 VGPRs) and
-  // 4x the weight bytes through L1: 56x56x256 -> 256 took 54 us packed and
-  // 60-65 us prepared.  Rows of 4 words without LDS staging also pay
-  // (16x16x128 -> 256 at batch 64: 6.3 -> 5.9 us); with LDS staging the
-  // packed words are expanded once per block, which prepared operands
-  // cannot match (48x48x128 -> 128 pool at batch 256: 48 against 54 us).
-  p.prep = tf == 1 || g.Cw <= 2 || (g.Cw <= 4 && !lds);
-  return p;
-}
-
 // wprep: prepared weights (prepare_weights_kernel), used instead of the
 // packed w where plan_mfma says they pay, or null.
 hipError_t run_mfma(const ConvGeom& g, bool pool, const uint32_t* in, const uint32_t* w,
                     const void* wprep, const int32_t* thr, const uint32_t* flip, int32_t* sums,
                     uint32_t* bits, hipStream_t s) {
-  const Plan p = plan_mfma(g, pool);
+  const GeneralConvPlan p =
+      plan_general_conv(g, pool, options().lds_weights, options().late_thresholds);
   if (!p.prep) wprep = nullptr;
   Mfma32Args a;
   a.in = in;

@@ -29,7 +29,6 @@
 // many as it takes to give every compute unit an even share (56 x 56 x 256 at
 // batch 64 is 6.1 full runs per compute unit: with full runs only, a few
 // took 7).
-#include <algorithm>
 #include <type_traits>
 
 #include "fastdiv.hpp"
@@ -502,12 +501,12 @@ void launch_ks(const TileArgs& a, bool tail, unsigned grid, size_t lds, hipStrea
 
 bool launch_bconv_tile(const ConvGeom& g, const uint32_t* in, const uint32_t* w,
                        const int32_t* thr, const uint32_t* flip, int32_t* sums, uint32_t* bits,
-                       hipStream_t s, hipError_t* err) {
+                       bool prepared, hipStream_t s, hipError_t* err) {
   // The options pick variants of the general kernel.
   const bnn_options& o = options();
   if (o.xcd_order != 1 || o.lds_weights != -1 || o.late_thresholds != -1) return false;
   ConvTilePlan p;
-  if (!conv_tile_plan(g, sums != nullptr, &p)) return false;
+  if (!conv_tile_plan(g, sums != nullptr, bits != nullptr, prepared, &p)) return false;
   TileArgs a;
   a.in = in;
   a.w = w;
@@ -551,20 +550,12 @@ bool launch_bconv_tile(const ConvGeom& g, const uint32_t* in, const uint32_t* w,
   a.div_hv = make_fastdiv31(static_cast<uint32_t>(a.Hv));
   a.div_f = make_fastdiv31(static_cast<uint32_t>(p.fgs));
   a.units = static_cast<int32_t>(p.units);
-  // Full rounds of one 4-unit run per block slot, then a last round of
-  // shorter runs over all the slots.
-  const int64_t slots = std::max<int64_t>(512 / p.fgs / 8, 1);  // per XCD and filter group
-  const int64_t per_xcd = (p.units + 7) / 8;
-  const int64_t full = per_xcd / (4 * slots) * slots;
-  const int64_t rest = per_xcd - 4 * full;
-  // (runs of 2 units, two to a compute unit, take as long as half as many
-  // full ones, one to a compute unit)
-  a.nfull = static_cast<int32_t>(full);
-  const int64_t even = rest ? (rest + slots - 1) / slots : 1;
-  a.last = static_cast<int32_t>(even == 2 && full > 0 ? 4 : even);
-  a.xcd_units = static_cast<int32_t>(per_xcd);
+  const ConvTileRuns r = conv_tile_runs(p);
+  a.nfull = static_cast<int32_t>(r.full);
+  a.last = static_cast<int32_t>(r.last);
+  a.xcd_units = static_cast<int32_t>(r.per_xcd);
   const unsigned grid =
-      static_cast<unsigned>(8 * p.fgs * (full + (rest + a.last - 1) / a.last));
+      static_cast<unsigned>(8 * p.fgs * (r.full + (r.rest + r.last - 1) / r.last));
   const bool tail = g.C != 64 * p.ks * p.nchunk;
   switch (p.ks) {
     case 1: launch_ks<1>(a, tail, grid, p.lds, s); break;

@@ -54,12 +54,14 @@ hipError_t launch_bconv_mfma(const ConvGeom& g, const uint32_t* in,
 
 // Binary conv on the matrix cores with the input rows of a run of pixels
 // staged once in LDS as fp4 operands (bconv_tile.hip), sums and / or bits.
+// prepared: the general kernel would get prepared weights (this one reads the
+// packed w).
 // Returns false, with nothing launched, for shapes the general kernel is the
 // faster for; otherwise launches and sets *err.  Assumes
 // bconv_mfma_supported(g).
 bool launch_bconv_tile(const ConvGeom& g, const uint32_t* in, const uint32_t* w,
                        const int32_t* thr, const uint32_t* flip, int32_t* sums, uint32_t* bits,
-                       hipStream_t s, hipError_t* err);
+                       bool prepared, hipStream_t s, hipError_t* err);
 
 // Prepared ("operand form") conv weights for the matrix-core kernel: 16-byte
 // entries [ceil(F / 32)][KH][KW][Cp][32] (Cp = Cw when C % 64 == 0, else

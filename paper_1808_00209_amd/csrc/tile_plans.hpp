@@ -12,6 +12,149 @@
 
 namespace bnn {
 
+// --------------------------------------------- general conv (bconv_mfma.hip)
+
+// Launch plan of the matrix-core conv for a geometry: words per lane and
+// iteration (vw), filter tiles per wave (tf), K split (ks), weights through
+// LDS (lds), late threshold staging (late), C not a multiple of 64 (tail),
+// and whether prepared weights pay (prep).
+struct GeneralConvPlan {
+  int vw, tf, ks;
+  bool lds, late, tail, short8, prep;
+  int iters;       // iterations of 2 vw words over the window
+  int64_t groups;  // 64-pixel groups
+};
+
+inline GeneralConvPlan plan_general_conv(const ConvGeom& g, bool pool, int lds_weights,
+                                         int late_thresholds) {
+  GeneralConvPlan p;
+  const int64_t items = pool ? 4 * int64_t{g.N} * g.Hp * g.Wp : int64_t{g.N} * g.Ho * g.Wo;
+  const int64_t groups = (items + 63) / 64;
+  const int64_t ftiles = (g.F + 31) / 32;
+  // Words per lane, row and iteration: 8-word chunks (128-bit loads) where
+  // the channels allow, which halves the vector-memory instructions per MFMA
+  // (the texture-address unit is the busiest unit of the small grids), but
+  // not when that leaves fewer than 8 iterations to split.
+  // C not a multiple of 64: the loop walks Cc >= Cw words per tap, whole
+  // chunks of 2 VW words, with the words past Cw zeroed and every word
+  // loaded on its own (bconv_mfma32_kernel, TAIL).  VW is the largest of 4,
+  // 2, 1 whose padding stays within 1/8 of the row.
+  p.tail = g.C % 64 != 0;
+  int vw = g.Cw % 8 == 0 ? 4 : g.Cw % 4 == 0 ? 2 : 1;
+  // Windows of at most 4 eight-word chunks (K <= 1024 bits, e.g. FC layers
+  // of 1024 inputs) on grids too small to fill the chip keep 8-word chunks
+  // and no K split: there the split's LDS reduction costs more than it
+  // hides (1024 -> 1024 and 1024 -> 10 at 64 rows: 4.15 and 4.30 us against
+  // 4.42 and 4.57 us with 2-word chunks split 4 ways).
+  const int chunks8 = g.KH * g.KW * (g.Cw / 8);
+  p.short8 = !p.tail && vw == 4 && chunks8 <= 4 && groups * ftiles < 1024;
+  if (vw == 4 && chunks8 < 8 && !p.short8) vw = 2;
+  // Option lds_weights = 1 asks for the LDS-weights kernel wherever no K
+  // split is used; it takes chunks of at most 2 words.
+  if (lds_weights == 1 && vw == 4) vw = 2;
+  if (p.tail) {
+    vw = 1;
+    for (int t = 4; t >= 2 && vw == 1; t /= 2)
+      if (((g.Cw + 2 * t - 1) / (2 * t) * (2 * t) - g.Cw) * 8 <= g.Cw) vw = t;
+  }
+  p.vw = vw;
+  const int Cc = (g.Cw + 2 * vw - 1) / (2 * vw) * (2 * vw);
+  const int iters = g.KH * g.KW * (Cc / (2 * vw));
+  p.iters = iters;
+  p.groups = groups;
+
+  // Tile shape and K split: 64-filter wave tiles down to ~1 wave per SIMD
+  // (1024 waves), then 32-filter tiles with a K split over up to 4 waves
+  // until there are ~1 (8-word chunks) or ~2 (smaller chunks) waves per
+  // SIMD, keeping at least 2 iterations per wave.  Splitting 8 ways never
+  // beat 4 (the LDS reduction then costs more than it hides).  With 2-word
+  // chunks, grids of >= 4096 64-filter tiles stage the weights through LDS
+  // (5-20 % faster there, slower on smaller grids); 8-word chunks without
+  // staging were as fast or faster wherever the channels allow them.  All
+  // measured on every layer shape of the networks here.
+  int tf = 2, ks = 1;
+  if (g.F % 64 != 0 || groups * (g.F / 64) < 1024) {
+    tf = 1;
+    const int64_t target = vw == 4 ? 1024 : 2048;
+    while (!p.short8 && ks < 4 && groups * ftiles * ks < target && iters >= 4 * ks) ks *= 2;
+  }
+  bool lds = lds_weights == -1 ? vw <= 2 && tf == 2 && groups * (g.F / 64) >= 4096
+                                    : lds_weights == 1;
+  if (ks > 1 || vw == 4) lds = false;
+  if (p.tail) {
+    tf = 1;
+    lds = false;
+    if (ks > 4) ks = 4;
+  }
+  p.tf = tf;
+  p.ks = ks;
+  p.lds = lds;
+  // Thresholds staged after the main loop on grids of at most 2 waves per
+  // SIMD (2048 waves) with 32-filter tiles, at kernel start otherwise, where
+  // the accumulators can then start from them (16x16x128 -> 256 and
+  // 16x16x256 -> 256 pool at batch 64: 5.98 / 7.50 us early against
+  // 6.25 / 7.94 us late; 8x8x256 -> 512 with 32-filter tiles: 6.11 us late,
+  // 6.22 us early).  Option late_thresholds overrides.
+  const int64_t waves = (groups + 3) / 4 * 4 * ((g.F + 32 * tf - 1) / (32 * tf));
+  p.late = p.tail || (late_thresholds == -1 ? waves <= 2048 && tf == 1
+                                                 : late_thresholds == 1);
+  // Prepared weights where they pay (graph-timed on every conv shape of the
+  // networks here): 32-filter tiles, where a wave's vector-ALU work per MFMA
+  // then drops from 12 to 8 instructions (8x8x512 -> 512 pool at batch 64:
+  // 9.7 -> 8.2 us; 8x8x256 -> 512: 6.6 -> 6.0 us), and rows of at most 2
+  // words.  With 64-filter tiles over 256 or more channels the prepared
+  // operands' registers cost a wave per SIMD (180 against 154 VGPRs) and
+  // 4x the weight bytes through L1: 56x56x256 -> 256 took 54 us packed and
+  // 60-65 us prepared.  Rows of 4 words without LDS staging also pay
+  // (16x16x128 -> 256 at batch 64: 6.3 -> 5.9 us); with LDS staging the
+  // packed words are expanded once per block, which prepared operands
+  // cannot match (48x48x128 -> 128 pool at batch 256: 48 against 54 us).
+  p.prep = tf == 1 || g.Cw <= 2 || (g.Cw <= 4 && !lds);
+  return p;
+}
+
+// Estimated time of the general conv in microseconds at default options, for
+// C not a multiple of 64, fitted (non-negative least squares on relative
+// errors) to graph-timed runs of 8000 random shapes (32 to 600 channels, 33 to
+// 512 filters, 1 to 30 taps, 4 to 300 us; half of the estimates within 6 %,
+// nine in ten within 16 %): a start, then per pass the latency of a wave's
+// k-steps, what its vector instructions and MFMAs take from its SIMD (more
+// where rows of a multiple of 32 bytes meet in the same cache banks), and the
+// sums' bytes.  prep: with prepared weights.
+inline double general_conv_us(const ConvGeom& g, bool sums, bool bits, bool prep) {
+  struct Cost {
+    double start, latency, step, wave, row32, split;
+  };
+  static constexpr Cost kPacked[3] = {{3.16, 0.142, 0.132, 0.278, 0.026, 0.10},
+                                      {3.34, 0.083, 0.096, 0.472, 0.041, 0.02},
+                                      {3.76, 0.078, 0.076, 1.010, 0.050, 0.00}};
+  static constexpr Cost kPrepared[3] = {{3.07, 0.110, 0.096, 0.278, 0, 0.13},
+                                        {3.32, 0.041, 0.074, 0.348, 0, 0.10},
+                                        {3.24, 0.037, 0.055, 0.533, 0, 0.00}};
+  const bool row32 = g.KH * g.KW * g.Cw % 8 == 0;
+  // odd pooled sizes with sums: one pass for the sums, one for the bits
+  const bool two = g.pool == 2 && sums && ((g.Ho & 1) || (g.Wo & 1));
+  double us = 0;
+  for (int pass = 0; pass < (two && bits ? 2 : 1); ++pass) {
+    const bool pool = g.pool == 2 && !(two && pass == 0), s = sums && pass == 0;
+    const GeneralConvPlan p = plan_general_conv(g, pool, -1, -1);
+    const bool pr = prep && p.prep;
+    const int v = p.vw == 4 ? 2 : p.vw - 1;
+    const Cost& c = pr ? kPrepared[v] : kPacked[v];
+    const int64_t fy = (g.F + 32 * p.tf - 1) / (32 * p.tf);
+    const int64_t pixel_waves = p.ks == 1 ? (p.groups + 3) / 4 * 4 : p.groups * p.ks;
+    const double waves = static_cast<double>(pixel_waves * fy) / 1024;  // per SIMD
+    const double steps = static_cast<double>(p.iters) * p.vw / p.ks;
+    us += c.start + c.latency * steps +
+          waves * (steps * (c.step + (row32 ? c.row32 : 0)) + c.wave + (p.ks > 1 ? c.split : 0));
+    if (s) {
+      const double mb = 4e-6 * g.N * g.Ho * g.Wo * g.F;
+      us += 1.7 + mb * (g.F % 4 ? 0.58 : 0.17);
+    }
+  }
+  return us;
+}
+
 // ------------------------------------------- staged-tile conv (bconv_tile.hip)
 
 // LDS words per pixel of a wave's 64 sums (16-byte aligned, odd in 16s).
@@ -120,29 +263,110 @@ inline ConvTilePlan plan_conv_tile(const ConvGeom& g, bool sums) {
   }
   return p;
 }
-// Where the staged-tile kernel is the faster one (graph-timed against the general kernel
-// over 140 random shapes, 2 to 250 images, 32 to 512 channels and filters, 1x1
-// to 5x5).
-inline bool conv_tile_pays(const ConvGeom& g, const ConvTilePlan& p) {
+// The runs of an XCD's units: `full` of 4 units, as many rounds of one per
+// block slot as there are whole ones, then runs of `last` units that give
+// every slot an even share.
+struct ConvTileRuns {
+  int64_t slots, per_xcd, full, last, rest;
+};
+
+inline ConvTileRuns conv_tile_runs(const ConvTilePlan& p) {
+  ConvTileRuns r;
+  r.slots = std::max<int64_t>(512 / p.fgs / 8, 1);  // per XCD and filter group
+  r.per_xcd = (p.units + 7) / 8;
+  r.full = r.per_xcd / (4 * r.slots) * r.slots;
+  r.rest = r.per_xcd - 4 * r.full;
+  // (runs of 2 units, two to a compute unit, take as long as half as many
+  // full ones, one to a compute unit)
+  const int64_t even = r.rest ? (r.rest + r.slots - 1) / r.slots : 1;
+  r.last = even == 2 && r.full > 0 ? 4 : even;
+  return r;
+}
+
+// Virtual rows that a run of `units` units may touch.
+inline int conv_tile_rows(const ConvGeom& g, const ConvTilePlan& p, int units) {
+  const int rh = g.pool == 2 ? 2 : 1;
+  const int per = std::max(units * (4 >> p.wfl) * 32 / (rh * rh), 1);
+  const int span = 1 + (per - 1 + p.Ws - 1) / p.Ws;
+  const int cross = (span - 1 + p.Hw - 1) / p.Hw;
+  return rh * span + g.KH - 1 + cross * std::max(p.H + 2 * g.pad - rh * p.Hw, 0);
+}
+
+// Estimated time of the staged-tile conv in microseconds, C not a multiple of
+// 64, fitted like general_conv_us and as close: rounds of runs, each its
+// start, its taps' and chunks' latencies, the staging's vector instructions
+// and its units' MFMAs (which take four times as long with two blocks on a
+// compute unit as with one: the last round of at most 256 blocks), then the
+// sums.  The 4-k-step form spills registers, most of all with sums.
+inline double conv_tile_us(const ConvGeom& g, const ConvTilePlan& p, bool sums) {
+  const ConvTileRuns r = conv_tile_runs(p);
+  const double full = static_cast<double>(r.full / r.slots);
+  const int last = r.rest ? static_cast<int>(r.last) : 0;
+  const bool paired = r.rest && (r.rest + r.last - 1) / r.last * p.fgs * 8 > 256;
+  const int taps = g.KH * g.KW, steps = taps * p.ks * p.nchunk;
+  const double rounds = full + (last ? 1 : 0);
+  const double staged = full * conv_tile_rows(g, p, 4) * p.cols / 128.0 +
+                        (last ? conv_tile_rows(g, p, last) * p.cols / 128.0 : 0);
+  const double units2 = 4 * full + (paired ? last : 0), units1 = paired ? 0 : last;
+  const double units = units2 + 0.4 * units1;
+  double us = 2.25 + rounds * (1.58 + p.nchunk * (0.88 + 0.145 * taps)) +
+              staged * p.nchunk * p.ks * 0.08 + steps * (0.058 * units2 + 0.015 * units1);
+  if (taps * g.Cw % 8 == 0 && p.ks <= 2) us += 0.010 * units * steps;  // rows of 32 bytes
+  if (p.ks == 4) us += 0.012 * units * steps;
+  if (sums) {
+    const double mb = 4e-6 * g.N * g.Ho * g.Wo * g.F;
+    us += 2.03 + mb * ((g.F % 4 ? 0.31 : 0.129) + (p.ks == 4 ? 0.078 : 0));
+  }
+  // (chunks of one k-step: the loop's start and end outweigh it)
+  return p.ks == 1 && p.nchunk >= 3 ? 1.2 * us : us;
+}
+
+// Where this kernel is the faster one.  prep: the general kernel would get
+// prepared weights.
+inline bool conv_tile_pays(const ConvGeom& g, bool sums, bool bits, bool prep,
+                           const ConvTilePlan& p) {
   if (!p.ok || p.fgs > 64) return false;
+  const int taps = g.KH * g.KW, steps = taps * p.ks;
   // C not a multiple of 64: the general kernel loads word by word and pads in
-  // its loop (x1.04 to x2.4 here from 256 units on; 160 -> 256, 5x5 at 19 x 64
-  // x 64: 108 -> 47 us).
-  if (g.C % 64 != 0) return p.units * p.fgs >= kConvTileTailUnits;
+  // its loop, which this one avoids on large grids (160 -> 256, 5x5 at 19 x
+  // 64 x 64: 108 -> 47 us) and does not on small ones, at padded row lengths
+  // or against prepared weights (49 -> 414 3x4 at 12 x 29 x 59: 13.0 us there,
+  // 15.1 here; 459 -> 256 3x3 at 28 x 45 x 12, prepared: 12.8 and 18.5; 195 ->
+  // 256 1x1 at 194 x 13 x 15 with sums: 16.7 and 19.4): the smaller estimate,
+  // less a margin where the estimates favour this kernel too often (even
+  // windows, whose filters' words collide in the caches, 1x1 and prepared
+  // weights).
+  if (g.C % 64 != 0) {
+    if (p.units * p.fgs < kConvTileTailUnits) return false;
+    const double margin =
+        (taps == 1 ? 0.92 : taps % 2 == 0 ? 0.85 : 1.0) * (prep ? 0.95 : 1.0);
+    return conv_tile_us(g, p, sums) < margin * general_conv_us(g, sums, bits, prep);
+  }
   // Otherwise: a neighbourhood to stage for, one channel chunk (two halve the
   // work per staging: 512 -> 512 at 28 x 28 x 34 ran 8 % slower here), at
   // least 9 k-steps per run's pixel (18 when pooling: 64 -> 256 pooled 3 %
-  // slower, 64 -> 128 without pooling 9 % faster), at least two waves along
-  // the filters of which at most 1/8 is padding, and a full run for every
-  // block slot (smaller grids are faster with the general kernel's K split).
-  const int steps = g.KH * g.KW * p.ks;
+  // slower, 64 -> 128 without pooling the same to 10 % faster), at least two
+  // waves along the filters of which at most 1/8 is padding, and a full run
+  // for every block slot (smaller grids are faster with the general kernel's
+  // K split).  Bits of windows of a multiple of 4 taps, whose filters' rows
+  // are a multiple of 32 bytes, only at 192 channels or from 48 k-steps on (64
+  // -> 128 4x4 at 141 x 55 x 105: 50.7 us there, 65.5 here; 256 -> 512 2x2 at
+  // 5 x 38 x 586: 28.0 and 32.1; with sums this kernel is the faster one).
+  if (!sums && taps % 4 == 0 && g.C != 192 && steps < 48) return false;
+  const int64_t units = p.units * p.fgs;
+  // (a second round of 1/8 to 1/3 of the units takes most of a full round's
+  // time: 128 -> 256 at 32 x 26 x 98, 2548 units, 14.9 us there, 17.2 here; sums
+  // gain more than that, but at 256 channels, and so do 192 channels)
+  if (g.F % 64 == 0 && g.C != 192 && (!sums || g.C == 256) && units >= 2304 &&
+      units < (steps <= 18 ? 3072 : 2688))
+    return false;
   return p.nchunk == 1 && steps >= (g.pool == 2 ? 18 : 9) && p.wfl >= 1 &&
-         8 * p.fgs * (64 << p.wfl) <= 9 * int64_t{g.F} && p.units * p.fgs >= kConvTileUnits;
+         8 * p.fgs * (64 << p.wfl) <= 9 * int64_t{g.F} && units >= kConvTileUnits;
 }
 
 // Whether the staged-tile kernel takes the conv, and how.  What can be told
 // without a plan comes first (a plan takes 1 to 3 us of host time).
-inline bool conv_tile_plan(const ConvGeom& g, bool sums, ConvTilePlan* p) {
+inline bool conv_tile_plan(const ConvGeom& g, bool sums, bool bits, bool prep, ConvTilePlan* p) {
   // (With 32 filters half of every wave's would be padding; a 1x1 conv has
   // nothing to stage for unless its rows are ragged, and it lost there too
   // when pooled (96 -> 192 at 64 x 64 x 120: 26 -> 31 us) or of several chunks
@@ -155,7 +379,7 @@ inline bool conv_tile_plan(const ConvGeom& g, bool sums, ConvTilePlan* p) {
   const int64_t outputs = int64_t{g.N} * (g.Ho + 1) * (g.Wo + 1) * ((g.F + 63) / 64 * 64);
   if (outputs / 8192 < (ragged ? kConvTileTailUnits : kConvTileUnits) * 2 / 3) return false;
   *p = plan_conv_tile(g, sums);
-  return conv_tile_pays(g, *p);
+  return conv_tile_pays(g, sums, bits, prep, *p);
 }
 
 }  // namespace bnn

@@ -1,6 +1,7 @@
 """The plan of the staged-tile conv, on the host: its cost does not grow with
-the map, and no run of it reads or stages outside the LDS tile, for any window
-(square or not), pooled or not, with and without sums (CPU only)."""
+the map, no run of it reads or stages outside the LDS tile, for any window (square
+or not), pooled or not, with and without sums, and it is taken where it
+measured faster than the general kernel (CPU only)."""
 import random
 
 import numpy as np
@@ -80,3 +81,48 @@ def test_runs_stay_inside_their_lds_tile(sums):
         assert cut.min() == 1 and seen.max() == 1, shape
         assert wp * 32 == unit
     assert planned > 300
+
+
+# Graph-timed on one card: the general kernel's time and the staged-tile
+# kernel's, in microseconds.  (N, H, W, C, F, KH, KW, pad, pool), sums, bits,
+# prepared weights, general, staged tile.
+MEASURED = [
+    ((93, 54, 49, 64, 256, 3, 4, 1, 0), 0, 1, 0, 30.8, 36.8),
+    ((21, 24, 434, 64, 512, 4, 4, 2, 0), 0, 1, 0, 66.1, 83.6),
+    ((171, 51, 9, 64, 512, 4, 4, 0, 0), 0, 1, 1, 19.8, 23.4),
+    ((32, 26, 98, 128, 256, 3, 3, 1, 0), 0, 1, 0, 14.9, 17.2),
+    ((77, 6, 18, 41, 203, 1, 1, 0, 0), 0, 1, 0, 3.8, 4.4),
+    ((67, 39, 14, 204, 64, 1, 1, 0, 0), 1, 0, 0, 8.0, 9.4),
+    ((2, 53, 40, 208, 512, 1, 1, 0, 0), 0, 1, 1, 4.7, 5.6),
+    ((11, 31, 31, 249, 256, 1, 1, 0, 0), 1, 0, 1, 7.9, 9.4),
+    ((113, 39, 33, 96, 64, 2, 1, 0, 2), 0, 1, 0, 6.5, 7.9),
+    ((99, 48, 5, 491, 65, 1, 2, 0, 0), 1, 0, 0, 9.9, 12.4),
+    ((13, 60, 30, 238, 128, 1, 3, 0, 0), 0, 1, 1, 5.4, 6.7),
+    ((66, 16, 12, 467, 256, 5, 2, 0, 0), 1, 1, 1, 17.0, 20.8),
+    ((60, 29, 11, 274, 156, 3, 3, 0, 2), 0, 1, 0, 11.6, 14.5),
+    ((48, 14, 14, 277, 512, 5, 5, 0, 0), 1, 0, 0, 37.5, 49.2),
+    ((6, 44, 53, 325, 242, 5, 5, 0, 2), 0, 1, 1, 23.4, 29.4),
+    ((28, 45, 12, 459, 256, 3, 3, 1, 0), 0, 1, 1, 12.8, 18.5),
+    ((147, 10, 43, 192, 512, 1, 7, 0, 0), 0, 1, 0, 26.0, 18.9),
+    ((100, 24, 56, 192, 256, 5, 2, 1, 2), 1, 0, 0, 64.1, 41.1),
+    ((81, 24, 56, 256, 470, 3, 3, 1, 2), 0, 1, 0, 66.0, 46.2),
+    ((64, 56, 56, 256, 256, 3, 3, 1, 0), 0, 1, 1, 48.4, 41.9),
+    ((163, 35, 35, 256, 256, 3, 3, 1, 2), 1, 1, 0, 127.6, 81.0),
+    ((116, 61, 61, 64, 473, 3, 3, 0, 0), 0, 1, 1, 107.6, 76.3),
+    ((58, 48, 33, 128, 512, 3, 3, 1, 2), 1, 0, 1, 71.8, 46.0),
+    ((7, 45, 61, 160, 200, 3, 3, 1, 2), 1, 1, 0, 29.8, 13.7),
+    ((173, 12, 12, 255, 256, 1, 1, 0, 0), 0, 1, 0, 9.9, 6.6),
+    ((49, 33, 33, 121, 285, 1, 1, 0, 0), 1, 0, 0, 50.3, 33.7),
+    ((18, 19, 452, 150, 512, 1, 1, 0, 0), 0, 1, 1, 30.1, 21.9),
+    ((30, 37, 16, 215, 512, 1, 7, 0, 0), 0, 1, 0, 18.6, 10.0),
+    ((68, 12, 12, 204, 512, 3, 4, 1, 0), 0, 1, 1, 20.8, 12.6),
+    ((105, 7, 55, 294, 64, 3, 4, 0, 2), 1, 1, 1, 24.9, 15.4),
+    ((238, 37, 32, 180, 54, 5, 5, 2, 2), 0, 1, 0, 88.0, 43.9),
+    ((169, 56, 15, 300, 64, 5, 5, 2, 2), 0, 1, 1, 69.6, 41.2),
+]
+
+
+@pytest.mark.parametrize("case", MEASURED, ids=[str(c[:4]) for c in MEASURED])
+def test_the_faster_conv_kernel_is_taken(case):
+    shape, sums, bits, prepared, general, tile = case
+    assert (tile_plans.conv_tile(shape, sums, bits, prepared) is not None) == (tile < general)

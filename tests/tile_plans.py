@@ -38,9 +38,9 @@ extern "C" void conv_tile_cheapest(const int32_t* shape, int sums, int64_t* o) {
 }
 
 // 1 where the staged-tile kernel takes the shape.
-extern "C" int conv_tile_takes(const int32_t* shape, int sums, int64_t* o) {
+extern "C" int conv_tile_takes(const int32_t* shape, int sums, int bits, int prep, int64_t* o) {
   ConvTilePlan p = {};
-  const bool r = conv_tile_plan(geom(shape), sums != 0, &p);
+  const bool r = conv_tile_plan(geom(shape), sums != 0, bits != 0, prep != 0, &p);
   fill(p, o);
   return r;
 }
@@ -52,7 +52,7 @@ extern "C" double conv_tile_host_us(const int32_t* shape, int sums, int reps) {
   for (int i = 0; i < reps; ++i) {
     const auto t0 = std::chrono::steady_clock::now();
     ConvTilePlan p = {};
-    volatile bool r = conv_tile_plan(g, sums != 0, &p);
+    volatile bool r = conv_tile_plan(g, sums != 0, true, false, &p);
     (void)r;
     const auto t1 = std::chrono::steady_clock::now();
     best = std::min(best, std::chrono::duration<double, std::micro>(t1 - t0).count());
@@ -91,11 +91,12 @@ def cheapest(shape, sums):
     return _dict(o)
 
 
-def conv_tile(shape, sums):
+def conv_tile(shape, sums, bits=True, prepared=False):
     """The plan with which the staged-tile kernel takes (N, H, W, C, F, KH, KW,
     pad, pool), or None where another kernel does."""
     o = (ctypes.c_int64 * 20)()
-    return _dict(o) if lib().conv_tile_takes(_shape(*shape), int(sums), o) else None
+    takes = lib().conv_tile_takes(_shape(*shape), int(sums), int(bits), int(prepared), o)
+    return _dict(o) if takes else None
 
 
 def conv_tile_host_us(shape, sums, reps=50):
