@@ -18,7 +18,6 @@
 // 4096 x 8192 -> 4096, bits: 133 us in the FC kernel, 50 us here (5.5e15
 // operations a second; the matrix cores are busy 86 % of the waves' cycles,
 // at a clock that drops to about 1.5 GHz).
-#include <algorithm>
 #include <type_traits>
 
 #include "fastdiv.hpp"
@@ -26,6 +25,7 @@
 #include "fp4_expand.hpp"
 #include "kernels.hpp"
 #include "lane_ops.hpp"
+#include "tile_plans.hpp"
 
 namespace bnn {
 namespace {
@@ -33,10 +33,9 @@ namespace {
 constexpr int kNT = 256;
 constexpr int kKS = 4;             // k-steps (64 bits) per chunk
 constexpr int kPS = 2 * kKS + 1;   // LDS entries per staged row (odd: no conflicts)
-constexpr int kRows = 128;         // data rows per block, at most (staged, used or not)
+constexpr int kRows = kFcTileRows;  // data rows per block, at most (staged, used or not)
 constexpr int kSumStride = 36;     // LDS words per row of a sums tile
 constexpr int kRsrcWord3 = 0x00020000;
-constexpr int kCUs = 256;          // compute units of the chip
 
 struct BtArgs {
   const uint32_t* A;      // [M][Kw]
@@ -324,47 +323,9 @@ void launch_pt(const BtArgs& a, unsigned grid, size_t lds, hipStream_t s) {
 bool launch_bfc_tile(int64_t M, int64_t N, int64_t K, const uint32_t* A, const uint32_t* B,
                      const int32_t* thr, const uint32_t* flip, int32_t* sums, uint32_t* bits,
                      hipStream_t s, hipError_t* err) {
+  FcTilePlan p;
+  if (!fc_tile_plan(M, N, K, sums != nullptr, bits != nullptr, &p)) return false;
   const int64_t Kw = (K + 31) / 32;
-  if (K < 1024 || K >= (1 << 22) || M * Kw * 4 >= (int64_t{1} << 31) - 4096 ||
-      N * Kw * 4 >= (int64_t{1} << 31) - 4096)
-    return false;
-  // Grids of more than 1024 32 x 32 tiles, where the FC kernel's 2 x 2 form
-  // needs a second round of workgroups (graph-timed, bits: 1100 x 8192 -> 1024
-  // 19.3 us there, 17.5 here; 1024 x 1024 -> 1024, one round, 4.6 and 6.2);
-  // where N is not a multiple of 64, more than 2048, below which the conv
-  // kernel is as fast (2048 x 4096 -> 1000 9.7 us there, 11.3 here; 4096 x
-  // 4100 -> 1000 22.4 and 15.3).
-  const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32);
-  if (t32 <= (N % 64 == 0 ? 1024 : 2048)) return false;
-  // Tile: 4 waves as 1 << wfl along the outputs (64 each) and the rest along
-  // the rows (32 PT each, at most 128 in all), by the estimated time: rounds of
-  // two blocks per compute unit, each its chunks' MFMAs (8 PT per chunk and
-  // wave, at about 38 / 44 / 60 cycles for PT = 4 / 2 / 1, whose weight
-  // expansion serves fewer MFMAs; at least the latency of a chunk) plus about
-  // 7000 cycles.
-  const int64_t chunks = (Kw + 7) / 8;
-  int best_wfl = -1, best_pt = 0;
-  double best = 0;
-  for (int wfl = 0; wfl <= 2; ++wfl) {
-    for (int pt = 4; pt >= 1; pt /= 2) {
-      const int wp = 4 >> wfl;
-      if (wp * pt * 32 > kRows) continue;
-      const int64_t tiles = ((N + (64 << wfl) - 1) / (64 << wfl)) *
-                            ((M + wp * pt * 32 - 1) / (wp * pt * 32));
-      // one block or two per compute unit
-      const double one = 8 * pt * (pt == 4 ? 38 : pt == 2 ? 44 : 60);
-      const double per = tiles <= kCUs ? std::max(one, 700.0) : std::max(1.9 * one, 1000.0);
-      const double cost = static_cast<double>((tiles + 2 * kCUs - 1) / (2 * kCUs)) *
-                          (chunks * per + 7000);
-      if (best_wfl < 0 || cost < best) {
-        best = cost;
-        best_wfl = wfl;
-        best_pt = pt;
-      }
-    }
-  }
-  const int wp = 4 >> best_wfl, bm = wp * best_pt * 32;
-  const int64_t ft = (N + (64 << best_wfl) - 1) / (64 << best_wfl), rt = (M + bm - 1) / bm;
   BtArgs a;
   a.A = A;
   a.B = B;
@@ -377,18 +338,18 @@ bool launch_bfc_tile(int64_t M, int64_t N, int64_t K, const uint32_t* A, const u
   a.Nw = static_cast<int32_t>((N + 31) / 32);
   a.Kw = static_cast<int32_t>(Kw);
   a.K = static_cast<int32_t>(K);
-  a.chunks = static_cast<int32_t>(chunks);
+  a.chunks = static_cast<int32_t>((Kw + 7) / 8);
   a.tmask = tail_mask(K);
-  a.wfl = best_wfl;
+  a.wfl = p.wfl;
   a.a_bytes = static_cast<int32_t>(M * Kw * 4);
   a.b_bytes = static_cast<int32_t>(N * Kw * 4);
-  a.rt = static_cast<int32_t>(rt);
-  a.div_g = make_fastdiv31(static_cast<uint32_t>(4 * ft));
-  a.div_r = make_fastdiv31(static_cast<uint32_t>(rt % 4 ? rt % 4 : 4));
-  const unsigned grid = static_cast<unsigned>((ft * rt + 7) / 8 * 8);
+  a.rt = static_cast<int32_t>(p.row_tiles);
+  a.div_g = make_fastdiv31(static_cast<uint32_t>(4 * p.output_tiles));
+  a.div_r = make_fastdiv31(static_cast<uint32_t>(p.row_tiles % 4 ? p.row_tiles % 4 : 4));
+  const unsigned grid = static_cast<unsigned>((p.output_tiles * p.row_tiles + 7) / 8 * 8);
   constexpr size_t lds = size_t{2} * kRows * kPS * 16;
   static_assert(lds >= 4 * 32 * kSumStride * 4, "the sums tiles fit");
-  switch (best_pt) {
+  switch (p.pt) {
     case 4: launch_pt<4>(a, grid, lds, s); break;
     case 2: launch_pt<2>(a, grid, lds, s); break;
     default: launch_pt<1>(a, grid, lds, s); break;

@@ -382,4 +382,74 @@ inline bool conv_tile_plan(const ConvGeom& g, bool sums, bool bits, bool prep, C
   return conv_tile_pays(g, sums, bits, prep, *p);
 }
 
+// ------------------------------------------------ many-row FC (bfc_tile.hip)
+
+constexpr int kFcTileRows = 128;  // data rows per block, at most
+constexpr int kCUs = 256;         // compute units of the chip
+
+// log2 of the waves along the outputs, 32-row tiles per wave, and the grid in
+// tiles.
+struct FcTilePlan {
+  int wfl, pt;
+  int64_t output_tiles, row_tiles;
+};
+
+// Whether the many-row kernel takes an FC layer / GEMM, and how.
+inline bool fc_tile_plan(int64_t M, int64_t N, int64_t K, bool sums, bool bits, FcTilePlan* p) {
+  const int64_t Kw = (K + 31) / 32;
+  if (K < 1024 || K >= (1 << 22) || M * Kw * 4 >= (int64_t{1} << 31) - 4096 ||
+      N * Kw * 4 >= (int64_t{1} << 31) - 4096)
+    return false;
+  // Grids of more than 1024 32 x 32 tiles, where the FC kernel's 2 x 2 form
+  // needs a second round of workgroups (graph-timed, bits: 1100 x 8192 -> 1024
+  // 19.3 us there, 17.5 here; 1024 x 1024 -> 1024, one round, 4.6 and 6.2);
+  // where N is not a multiple of 64, more than 2048, below which the conv
+  // kernel is as fast (2048 x 4096 -> 1000 9.7 us there, 11.3 here; 4096 x
+  // 4100 -> 1000 22.4 and 15.3).
+  const int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32);
+  if (t32 <= (N % 64 == 0 ? 1024 : 2048)) return false;
+  // Sums alone are as fast there up to 2048 tiles at the row lengths that the
+  // FC kernel splits evenly (262 x 2048 -> 4096 8.2 us there, 8.7 here; 4096
+  // bits 11.5 and 11.9, 1280 bits 7.5 and 6.7; with bits too 9.2 and 9.0).
+  if (!bits && t32 <= 2048 && (K == 1024 || K == 2048 || K == 4096)) return false;
+  // Up to 32 outputs, where at least half of a wave's 64 are padding, only
+  // where the conv kernel cannot take the rows in whole 256-bit chunks, and
+  // then long ones (bits, 66000 rows: 4096 -> 32 15.6 us there, 19.4 here; 1030
+  // -> 32 7.5 and 10.6; 5000 -> 32 26.9 and 23.7, -> 4 20.6 and 22.2; 16000 -> 16
+  // 61.8 and 54.6).
+  if (N <= 32 && (K % 256 == 0 || (K < 8192 && (K % 64 == 0 || N <= 16 || (!sums && K < 4096)))))
+    return false;
+  // Tile: 4 waves as 1 << wfl along the outputs (64 each) and the rest along
+  // the rows (32 PT each, at most 128 in all), by the estimated time: rounds of
+  // two blocks per compute unit, each its chunks' MFMAs (8 PT per chunk and
+  // wave, at about 38 / 44 / 60 cycles for PT = 4 / 2 / 1, whose weight
+  // expansion serves fewer MFMAs; at least the latency of a chunk) plus about
+  // 7000 cycles.
+  const int64_t chunks = (Kw + 7) / 8;
+  double best = 0;
+  p->wfl = -1;
+  for (int wfl = 0; wfl <= 2; ++wfl) {
+    for (int pt = 4; pt >= 1; pt /= 2) {
+      const int wp = 4 >> wfl;
+      if (wp * pt * 32 > kFcTileRows) continue;
+      const int64_t tiles = ((N + (64 << wfl) - 1) / (64 << wfl)) *
+                            ((M + wp * pt * 32 - 1) / (wp * pt * 32));
+      // one block or two per compute unit
+      const double one = 8 * pt * (pt == 4 ? 38 : pt == 2 ? 44 : 60);
+      const double per = tiles <= kCUs ? std::max(one, 700.0) : std::max(1.9 * one, 1000.0);
+      const double cost = static_cast<double>((tiles + 2 * kCUs - 1) / (2 * kCUs)) *
+                          (chunks * per + 7000);
+      if (p->wfl < 0 || cost < best) {
+        best = cost;
+        p->wfl = wfl;
+        p->pt = pt;
+      }
+    }
+  }
+  const int64_t rows = (4 >> p->wfl) * p->pt * 32;
+  p->output_tiles = (N + (64 << p->wfl) - 1) / (64 << p->wfl);
+  p->row_tiles = (M + rows - 1) / rows;
+  return true;
+}
+
 }  // namespace bnn

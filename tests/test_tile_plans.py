@@ -1,7 +1,7 @@
-"""The plan of the staged-tile conv, on the host: its cost does not grow with
-the map, no run of it reads or stages outside the LDS tile, for any window (square
-or not), pooled or not, with and without sums, and it is taken where it
-measured faster than the general kernel (CPU only)."""
+"""The plans of the tile kernels, on the host (CPU only).  The staged-tile conv's
+does not cost more on a wide map, no run of it reads or stages outside the LDS
+tile, for any window (square or not), pooled or not, with and without sums; and
+both kernels are taken where they measured faster than the others."""
 import random
 
 import numpy as np
@@ -126,3 +126,26 @@ MEASURED = [
 def test_the_faster_conv_kernel_is_taken(case):
     shape, sums, bits, prepared, general, tile = case
     assert (tile_plans.conv_tile(shape, sums, bits, prepared) is not None) == (tile < general)
+
+
+# The same for the many-row FC kernel: M, K, N, sums, bits, the FC or conv
+# kernel's time and the many-row kernel's.
+MEASURED_FC = [
+    (66000, 1024, 10, 0, 1, 7.2, 8.9), (150000, 1024, 32, 0, 1, 12.7, 14.2),
+    (66000, 4096, 32, 0, 1, 15.6, 19.4), (66000, 4096, 32, 1, 1, 19.0, 22.0),
+    (66000, 4096, 10, 1, 0, 15.5, 20.3), (66000, 1030, 32, 0, 1, 7.5, 10.6),
+    (66000, 5000, 4, 0, 1, 20.6, 22.2), (66000, 5000, 32, 0, 1, 26.9, 23.7),
+    (66000, 5000, 32, 1, 1, 30.4, 25.7), (66000, 16000, 16, 0, 1, 61.8, 54.6),
+    (66000, 4096, 48, 0, 1, 20.9, 20.4), (66000, 5000, 33, 0, 1, 32.2, 23.8),
+    (262, 2048, 4096, 1, 0, 8.2, 8.7), (262, 2048, 4096, 1, 1, 9.2, 9.0),
+    (262, 4096, 4096, 1, 0, 11.5, 11.9), (262, 1280, 4096, 1, 0, 7.5, 6.7),
+    (1100, 8192, 1024, 0, 1, 19.3, 17.5), (1024, 1024, 1024, 0, 1, 4.6, 6.2),
+    (2048, 4096, 1000, 0, 1, 9.7, 11.3), (4096, 4100, 1000, 0, 1, 22.4, 15.3),
+    (4096, 8192, 4096, 0, 1, 133.0, 50.0),
+]
+
+
+@pytest.mark.parametrize("case", MEASURED_FC, ids=[str(c[:3]) for c in MEASURED_FC])
+def test_the_faster_fc_kernel_is_taken(case):
+    M, K, N, sums, bits, other, tile = case
+    assert (tile_plans.fc_tile(M, K, N, sums, bits) is not None) == (tile < other)

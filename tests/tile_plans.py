@@ -45,6 +45,14 @@ extern "C" int conv_tile_takes(const int32_t* shape, int sums, int bits, int pre
   return r;
 }
 
+extern "C" int fc_tile_takes(int64_t M, int64_t K, int64_t N, int sums, int bits, int64_t* o) {
+  FcTilePlan p = {};
+  const bool r = fc_tile_plan(M, N, K, sums != 0, bits != 0, &p);
+  const int64_t v[] = {p.wfl, p.pt, p.output_tiles, p.row_tiles};
+  for (int i = 0; i < 4; ++i) o[i] = v[i];
+  return r;
+}
+
 // Least host time of a decision, in microseconds.
 extern "C" double conv_tile_host_us(const int32_t* shape, int sums, int reps) {
   const ConvGeom g = geom(shape);
@@ -101,3 +109,11 @@ def conv_tile(shape, sums, bits=True, prepared=False):
 
 def conv_tile_host_us(shape, sums, reps=50):
     return lib().conv_tile_host_us(_shape(*shape), int(sums), reps)
+
+
+def fc_tile(M, K, N, sums, bits):
+    """The plan with which the many-row FC kernel takes M x K -> N, or None."""
+    o = (ctypes.c_int64 * 4)()
+    i64 = ctypes.c_int64
+    takes = lib().fc_tile_takes(i64(M), i64(K), i64(N), int(sums), int(bits), o)
+    return dict(zip(("wfl", "pt", "output_tiles", "row_tiles"), o)) if takes else None
