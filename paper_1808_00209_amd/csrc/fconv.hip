@@ -544,7 +544,9 @@ __global__ __launch_bounds__(256) void fconv_mfma_kernel(FconvArgs a) {
       }
     // The sign bit of S - thr is set exactly when S < thr (thr_ceil_f32), the
     // complement of the output bit: one subtraction and one v_alignbit per
-    // value.  Lane row q holds 8 bits of each of a pixel's two words; three
+    // value.  (The matrix cores' NaN is 0xFFC00000, sign set, for NaN inputs of
+    // either sign and for infinities that meet, so a NaN sum's bit is 0 before
+    // the flip, as a comparison would give.)  Lane row q holds 8 bits of each of a pixel's two words; three
     // swaps leave row q with word q % 2 of tile q / 2 of a pair of tiles.
     const int w0 = f0 / 32, wq = w0 + (q & 1);
     const uint32_t nfl = ~fll[2 * g + (q & 1)];

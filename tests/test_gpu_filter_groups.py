@@ -62,3 +62,26 @@ def test_1x1_filter_groups(case):
     flip = _words(g, bnn.words(F))
     desc = bnn.conv_desc(N, H, W, C, F, 1, 1, 1, 0, 0)
     _same(lambda: bnn.bnn_bconv2d(desc, x, w, thr, flip, want_sums=False))
+
+
+@pytest.mark.parametrize("case", [(2, 24, 40, 3, 64, 0), (2, 24, 40, 1, 70, 2), (32, 64, 64, 3, 128, 0)],
+                         ids=str)
+@pytest.mark.parametrize("sums", [False, True])
+def test_first_layer_nan_sums_give_bit_0_before_flip(case, sums):
+    """S >= thr is false for a NaN sum whatever its sign bit: windows that hold
+    a NaN give the same bits as the vector-ALU kernel's comparison."""
+    N, H, W, C, F, pool = case
+    g = torch.Generator(device="cuda").manual_seed(H * W + F)
+    x = torch.randint(-1024, 1025, (N, H, W, C), generator=g, device="cuda").float() / 256
+    x[0, 5, 7, 0] = float("nan")
+    x.view(torch.int32)[-1, 9, 31, C - 1] = -0x400000  # a NaN with the sign bit set
+    w = _words(g, F, 3, 3, bnn.words(C))
+    thr = torch.randint(-12, 13, (F,), generator=g, device="cuda").to(torch.int32)
+    flip = _words(g, bnn.words(F))
+    desc = bnn.conv_desc(N, H, W, C, F, 3, 3, 1, 1, pool)
+    got = bnn.bnn_fconv2d_binw(desc, x, w, thr, flip, want_sums=sums)
+    with bnn.options(algo=bnn.ALGO_VALU):
+        ref = bnn.bnn_fconv2d_binw(desc, x, w, thr, flip, want_sums=sums)
+    assert torch.equal(got[1], ref[1])
+    if sums:
+        assert torch.equal(got[0].isnan(), ref[0].isnan()) and bool(got[0].isnan().any())
