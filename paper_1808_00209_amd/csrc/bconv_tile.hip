@@ -221,8 +221,10 @@ __global__ __launch_bounds__(kNT, 2) void bconv_tile_kernel(TileArgs a) {
         const bool ok = static_cast<unsigned>(y) < static_cast<unsigned>(a.H) &&
                         static_cast<unsigned>(x) < static_cast<unsigned>(a.W) &&
                         static_cast<int>(v) < a.vrows;
-        const uint32_t off = static_cast<uint32_t>(
-            (((static_cast<int>(n) * a.H + y) * a.W + x) * a.Cw + ch * CW + (tid & 1) * KS) * 4);
+        // (unsigned: near 2 GiB of input, the bytes past the last pixel's row)
+        const uint32_t off =
+            4u * static_cast<uint32_t>(((static_cast<int>(n) * a.H + y) * a.W + x) * a.Cw +
+                                       ch * CW + (tid & 1) * KS);
         load_words<KS>(xw[b], rin, ok ? off : kOutOfRange, 0u);
         dst[b] = static_cast<int>(row) * a.RS + col * PS + (tid & 1) * KS;
         row += a.step_row;  // kNT / 2 pixels on
