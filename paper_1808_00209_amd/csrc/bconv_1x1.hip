@@ -20,12 +20,12 @@
 #include "fastdiv.hpp"
 #include "fp4_expand.hpp"
 #include "kernels.hpp"
+#include "tile_plans.hpp"
 
 namespace bnn {
 namespace {
 
-constexpr int kPix = 256;   // pixels per block: 4 waves x 64
-constexpr int kCUs = 256;   // compute units of the chip
+constexpr int kPix = kConv1x1Pixels;  // pixels per block: 4 waves x 64
 constexpr int kMaxF = 1024;  // LDS: output rows 34 KB + thresholds 4 KB at F = 1024
 
 struct B1Args {
@@ -208,22 +208,8 @@ hipError_t launch_bconv1x1(const ConvGeom& g, const uint32_t* in, const uint32_t
   a.F = g.F;
   a.Fw = g.Fw;
   a.K = g.C;
-  // Filters per block: all of them, or a half or quarter (at least 4 chunks)
-  // where the finer grid's last round is that much fuller, at about 2 % per
-  // extra group for the operands built again.  56 x 56 x 256 -> 1024 at
-  // batch 64 is 3.06 whole-row blocks per compute unit, of which some took a
-  // fourth: 34.1 us, 29.6 in quarters.
   const int64_t pb = (int64_t{a.M} + kPix - 1) / kPix;
-  int groups = 1;
-  double best = 0;
-  for (int s2 = 1; s2 <= 4 && g.F % (64 * s2) == 0 && (s2 == 1 || g.F / s2 >= 256); s2 *= 2) {
-    const double cost =
-        static_cast<double>((pb * s2 + kCUs - 1) / kCUs) / s2 * (1 + 0.02 * (s2 - 1));
-    if (s2 == 1 || cost < best) {
-      best = cost;
-      groups = s2;
-    }
-  }
+  const int groups = conv1x1_groups(pb, g.F);
   a.fpb = g.F / groups;
   a.div_g = make_fastdiv31(static_cast<uint32_t>(groups));
   const unsigned blocks = static_cast<unsigned>((pb + 7) / 8 * 8 * groups);

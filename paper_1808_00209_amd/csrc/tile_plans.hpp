@@ -12,6 +12,8 @@
 
 namespace bnn {
 
+constexpr int kCUs = 256;  // compute units of the chip
+
 // --------------------------------------------- general conv (bconv_mfma.hip)
 
 // Launch plan of the matrix-core conv for a geometry: words per lane and
@@ -385,7 +387,6 @@ inline bool conv_tile_plan(const ConvGeom& g, bool sums, bool bits, bool prep, C
 // ------------------------------------------------ many-row FC (bfc_tile.hip)
 
 constexpr int kFcTileRows = 128;  // data rows per block, at most
-constexpr int kCUs = 256;         // compute units of the chip
 
 // log2 of the waves along the outputs, 32-row tiles per wave, and the grid in
 // tiles.
@@ -450,6 +451,30 @@ inline bool fc_tile_plan(int64_t M, int64_t N, int64_t K, bool sums, bool bits, 
   p->output_tiles = (N + (64 << p->wfl) - 1) / (64 << p->wfl);
   p->row_tiles = (M + rows - 1) / rows;
   return true;
+}
+
+// --------------------------------------------------- 1x1 conv (bconv_1x1.hip)
+
+constexpr int kConv1x1Pixels = 256;  // pixels per block
+
+// Groups that the F filters are split into, for `blocks` blocks of pixels: one
+// block takes all of them, or a half or quarter (at least 4 chunks of 64)
+// where the finer grid's last round is that much fuller, at about 2 % per
+// extra group for the operands built again.  56 x 56 x 256 -> 1024 at
+// batch 64 is 3.06 whole-row blocks per compute unit, of which some took a
+// fourth: 34.1 us, 29.6 in quarters.
+inline int conv1x1_groups(int64_t blocks, int F) {
+  int groups = 1;
+  double best = 0;
+  for (int n = 1; n <= 4 && F % (64 * n) == 0 && (n == 1 || F / n >= 256); n *= 2) {
+    const double cost = static_cast<double>((blocks * n + kCUs - 1) / kCUs) / n *
+                        (1 + 0.02 * (n - 1));
+    if (n == 1 || cost < best) {
+      best = cost;
+      groups = n;
+    }
+  }
+  return groups;
 }
 
 }  // namespace bnn

@@ -8,6 +8,7 @@ order and every sum and word must agree."""
 import pytest
 import torch
 
+import tile_plans
 from paper_1808_00209_amd import bnn
 
 pytestmark = pytest.mark.gpu
@@ -18,9 +19,15 @@ FCONV = [
     (32, 64, 64, 3, 128, 0), (3, 23, 45, 3, 70, 0), (2, 17, 33, 1, 36, 2), (1, 9, 31, 3, 192, 2),
 ]
 CONV1 = [
-    # N, H, W, C, F: 257 blocks of 256 pixels, the last one partial, or 769
-    (1, 257, 255, 256, 1024), (1, 257, 255, 128, 512), (1, 257, 255, 64, 768),
-    (3, 256, 257, 256, 512), (1, 256, 256, 64, 1024),
+    # N, H, W, C, F, filter groups: at least 65536 pixels, in blocks of 256.
+    # 259 blocks, the last one a single pixel
+    (1, 257, 257, 256, 1024, 4), (1, 257, 257, 128, 1024, 4), (1, 257, 257, 64, 512, 2),
+    # 529, 527 and 519 blocks, partial last ones
+    (2, 261, 259, 64, 1024, 4), (1, 311, 433, 256, 768, 2), (1, 401, 331, 128, 512, 2),
+    # whole last blocks; all filters per block
+    (3, 256, 257, 256, 512, 2), (1, 256, 256, 64, 1024, 1), (1, 257, 257, 256, 192, 1),
+    # a pixel fewer than the kernel's smallest grid: another kernel
+    (1, 257, 255, 256, 1024, 0),
 ]
 
 
@@ -54,7 +61,9 @@ def test_first_layer_filter_groups(case, sums, bits):
 
 @pytest.mark.parametrize("case", CONV1, ids=[str(c) for c in CONV1])
 def test_1x1_filter_groups(case):
-    N, H, W, C, F = case
+    N, H, W, C, F, groups = case
+    if groups:
+        assert N * H * W >= 65536 and tile_plans.conv1x1_groups(N * H * W, F) == groups
     g = torch.Generator(device="cuda").manual_seed(H * W + C + F)
     x, w = _words(g, N, H, W, bnn.words(C)), _words(g, F, 1, 1, bnn.words(C))
     thr = torch.randint(-20, 21, (F,), generator=g, device="cuda").to(torch.int32)

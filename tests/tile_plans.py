@@ -53,6 +53,10 @@ extern "C" int fc_tile_takes(int64_t M, int64_t K, int64_t N, int sums, int bits
   return r;
 }
 
+extern "C" int conv1x1_groups_of(int64_t pixels, int F) {
+  return conv1x1_groups((pixels + kConv1x1Pixels - 1) / kConv1x1Pixels, F);
+}
+
 // Least host time of a decision, in microseconds.
 extern "C" double conv_tile_host_us(const int32_t* shape, int sums, int reps) {
   const ConvGeom g = geom(shape);
@@ -117,3 +121,8 @@ def fc_tile(M, K, N, sums, bits):
     i64 = ctypes.c_int64
     takes = lib().fc_tile_takes(i64(M), i64(K), i64(N), int(sums), int(bits), o)
     return dict(zip(("wfl", "pt", "output_tiles", "row_tiles"), o)) if takes else None
+
+
+def conv1x1_groups(pixels, F):
+    """Filter groups of the 1x1 kernel (C = 64, 128 or 256, at least 65536 pixels)."""
+    return lib().conv1x1_groups_of(ctypes.c_int64(pixels), int(F))
