@@ -107,6 +107,7 @@ MEASURED = [
     ((100, 24, 56, 192, 256, 5, 2, 1, 2), 1, 0, 0, 64.1, 41.1),
     ((81, 24, 56, 256, 470, 3, 3, 1, 2), 0, 1, 0, 66.0, 46.2),
     ((64, 56, 56, 256, 256, 3, 3, 1, 0), 0, 1, 1, 48.4, 41.9),
+    ((256, 12, 12, 256, 512, 3, 3, 1, 2), 0, 1, 1, 20.4, 17.7),
     ((163, 35, 35, 256, 256, 3, 3, 1, 2), 1, 1, 0, 127.6, 81.0),
     ((116, 61, 61, 64, 473, 3, 3, 0, 0), 0, 1, 1, 107.6, 76.3),
     ((58, 48, 33, 128, 512, 3, 3, 1, 2), 1, 0, 1, 71.8, 46.0),
