@@ -356,13 +356,16 @@ inline bool conv_tile_pays(const ConvGeom& g, bool sums, bool bits, bool prep,
   // 5 x 38 x 586: 28.0 and 32.1; with sums this kernel is the faster one).
   if (!sums && taps % 4 == 0 && g.C != 192 && steps < 48) return false;
   const int64_t units = p.units * p.fgs;
-  // (a second round of more than 256 blocks, a compute unit's second ones, but
-  // at most 1/3 of the units takes most of a full round's time: 128 -> 256 at
-  // 32 x 26 x 98, 2548 units, 14.9 us there, 17.2 here; of 256 blocks it does
-  // not: 256 -> 512 pooled at 256 x 12 x 12, 2304 units, 20.4 and 17.7.  Sums
-  // gain more than that, but at 256 channels, and so do 192 channels)
+  // (Just past a full round of 2048 units the second one's runs of one unit, on
+  // more than one block per compute unit, take most of a full run's time: 128
+  // -> 256 at 32 x 26 x 98, 2548 units, 14.9 us there, 17.2 here.  On one block
+  // per compute unit they do not (256 -> 512 pooled at 256 x 12 x 12, 2304
+  // units, 20.4 and 17.7), and from 512 units on they are runs of 4 on fewer
+  // blocks (256 -> 256 from 2560 units 0.83 to 0.92 of the time); at 64
+  // channels a run's start weighs more.  Sums gain more than that, but at 256
+  // channels, and so do 192 channels.)
   if (g.F % 64 == 0 && g.C != 192 && (!sums || g.C == 256) && units > 2304 &&
-      units < (steps <= 18 ? 3072 : 2688))
+      units < (g.C == 64 ? 3072 : 2560))
     return false;
   return p.nchunk == 1 && steps >= (g.pool == 2 ? 18 : 9) && p.wfl >= 1 &&
          8 * p.fgs * (64 << p.wfl) <= 9 * int64_t{g.F} && units >= kConvTileUnits;
