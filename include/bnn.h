@@ -198,8 +198,10 @@ bnn_status bnn_bconv2d(const bnn_conv_desc* d, const uint32_t* in,
  *   bnn_prepare_weights: w [F][KH][KW][ceil(C/32)] u32 -> out (device,
  *     16-byte aligned, that many bytes).  Enqueued on `stream`.
  *   bnn_bconv2d_prepared: bnn_bconv2d with wprep = the prepared form of w.
- *     The packed w is still required: the vector-ALU ablation and the
- *     short-window 1x1 kernel read it.  wprep 16-byte aligned.
+ *     The packed w is still required: only the general matrix-core kernel
+ *     reads wprep; the other kernels (the staged-tile, 1x1 and 8x8 convs, the
+ *     vector-ALU ablation) read w, and the library takes whichever is the
+ *     faster for the shape.  wprep 16-byte aligned.
  * Errors: BNN_ERR_NULL, BNN_ERR_SHAPE, BNN_ERR_ALIGN, and as for bnn_bconv2d.
  */
 bnn_status bnn_prepared_weights_size(int32_t F, int32_t KH, int32_t KW, int32_t C,

@@ -137,22 +137,6 @@ __device__ __forceinline__ void conv_tile(const v4i* act, const int (&abase)[TP]
   }
 }
 
-// Sign bits of a 32 x 32 tile's accumulators (S - thr + 0.5): register e of
-// lane (h, c) holds filter 8 (e / 4) + 4 h + e % 4 at pixel c, which goes to
-// bit 31 - that filter.  Each lane half holds half of every pixel's word.
-__device__ __forceinline__ uint32_t sign_word(const v16f& acc, int h) {
-  uint32_t wd = 0u;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    uint32_t nib = 0u;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      nib = __builtin_amdgcn_alignbit(nib, __float_as_uint(acc[4 * g + r]), 31);
-    wd |= nib << (28 - 8 * g - 4 * h);
-  }
-  return wd;
-}
-
 // TH: second-conv output rows per block, 4, or 2 on grids smaller than the
 // chip (twice the blocks, each with 4 first-conv rows for 2 output rows
 // instead of 6 for 4).

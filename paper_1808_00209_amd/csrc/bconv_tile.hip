@@ -113,22 +113,6 @@ __device__ __forceinline__ void load_words(uint32_t (&v)[KS], __amdgpu_buffer_rs
   }
 }
 
-// Sign bits of a 32 x 32 tile (S - thr + 0.5): register e of lane (h, c)
-// holds filter 8 (e / 4) + 4 h + e % 4 of pixel c, which goes to bit 31 -
-// that filter.  Each lane half holds half of every pixel's word.
-__device__ __forceinline__ uint32_t sign_word(const v16f& acc, int h) {
-  uint32_t wd = 0u;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    uint32_t nib = 0u;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      nib = __builtin_amdgcn_alignbit(nib, __float_as_uint(acc[4 * g + r]), 31);
-    wd |= nib << (28 - 8 * g - 4 * h);
-  }
-  return wd;
-}
-
 // KS: k-steps (of 64 bits) per tap and channel chunk; lane half h feeds words
 // h KS .. h KS + KS - 1 of the chunk in both operands, so a lane's weight
 // words of a tap are one load.  SUMS: int32 sums wanted (bits too when

@@ -65,22 +65,6 @@ struct TailArgs {
 
 constexpr uint32_t kRsrcWord3 = 0x00020000;
 
-// Sign bits of a 32 x 32 tile's accumulators: register e of lane (h, c)
-// holds output 8 (e / 4) + 4 h + e % 4 of row c, which goes to bit 31 - that
-// output; each lane half holds half of every row's word.
-__device__ __forceinline__ uint32_t sign_word(const v16f& acc, int h) {
-  uint32_t wd = 0u;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    uint32_t nib = 0u;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      nib = __builtin_amdgcn_alignbit(nib, __float_as_uint(acc[4 * g + r]), 31);
-    wd |= nib << (28 - 8 * g - 4 * h);
-  }
-  return wd;
-}
-
 // The tail of an FC pair, run by every thread of the workgroup that holds
 // the first layer's 32 x 32 sums of rows m0 .. m0 + 31 and outputs
 // 32 ft .. 32 ft + 31 in `tile` (MFMA layout).  Wave 0 thresholds them into

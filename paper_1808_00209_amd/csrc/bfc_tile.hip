@@ -57,22 +57,6 @@ __device__ __forceinline__ v4i load4(__amdgpu_buffer_rsrc_t r, uint32_t voff, ui
   return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
 }
 
-// Sign bits of a 32 x 32 tile (S - thr + 0.5): register e of lane (h, c)
-// holds output 8 (e / 4) + 4 h + e % 4 of row c, which goes to bit 31 - that
-// output.  Each lane half holds half of every row's word.
-__device__ __forceinline__ uint32_t sign_word(const v16f& acc, int h) {
-  uint32_t wd = 0u;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    uint32_t nib = 0u;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      nib = __builtin_amdgcn_alignbit(nib, __float_as_uint(acc[4 * g + r]), 31);
-    wd |= nib << (28 - 8 * g - 4 * h);
-  }
-  return wd;
-}
-
 // PT: 32-row tiles per wave.  Lane half h feeds words 4 h .. 4 h + 3 of a
 // chunk in both operands, one 16-byte load per row and half.
 template <int PT, bool SUMS>

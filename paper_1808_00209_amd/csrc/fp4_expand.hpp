@@ -1,6 +1,7 @@
-// Packed +-1 words as fp4 (E2M1) matrix-core operands, shared by the binary
-// conv kernels: a value of the method is exactly +-1.0 in E2M1, and a word of
-// 32 values becomes the 4 registers of one lane's 32-value share of a
+// Packed +-1 words as fp4 (E2M1) matrix-core operands, and the packed bits of
+// their result tiles, shared by the binary conv and FC kernels: a value of the
+// method is exactly +-1.0 in E2M1, and a word of 32 values becomes the 4
+// registers of one lane's 32-value share of a
 // v_mfma_scale_f32_32x32x64_f8f6f4 operand.
 #pragma once
 
@@ -92,6 +93,23 @@ __device__ __forceinline__ void expand_words(const uint32_t (&w)[VW], uint32_t s
 #pragma unroll
     for (int v = 0; v < VW; v += 2) expand_pair(w[v], w[v + 1], smask, vfill, x[v], x[v + 1]);
   }
+}
+
+// Sign bits of a 32 x 32 tile's accumulators (S - thr + 0.5): register e of
+// lane (h, c) holds filter (or output) 8 (e / 4) + 4 h + e % 4 at pixel (or
+// row) c, which goes to bit 31 - that filter.  Each lane half holds half of
+// every pixel's word.
+__device__ __forceinline__ uint32_t sign_word(const v16f& acc, int h) {
+  uint32_t wd = 0u;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    uint32_t nib = 0u;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      nib = __builtin_amdgcn_alignbit(nib, __float_as_uint(acc[4 * g + r]), 31);
+    wd |= nib << (28 - 8 * g - 4 * h);
+  }
+  return wd;
 }
 
 }  // namespace bnn

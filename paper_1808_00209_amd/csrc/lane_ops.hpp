@@ -17,18 +17,12 @@ __device__ __forceinline__ uint32_t or_xor32(uint32_t x) {
   return x | r[0] | r[1];
 }
 
-// x of this lane OR x of lane ^ 16 (v_permlane16_swap, as above per 32 lanes).
-__device__ __forceinline__ uint32_t or_xor16(uint32_t x) {
-  const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-  return x | r[0] | r[1];
-}
-
 // Row r of a wave is lanes 16 r .. 16 r + 15.  v_permlane16_swap(a, b)
 // exchanges the odd rows of a with the even rows of b; v_permlane32_swap(a, b)
 // exchanges rows 2-3 of a with rows 0-1 of b.  For four words w0..w3 whose
 // rows each hold disjoint bits of one value per lane column, row q of the
 // result holds w_q ORed over its four rows (lane 16 q + c: column c).
-// Three swaps serve four words, where or_xor16 / or_xor32 take two per word.
+// Three swaps serve four words, where ORing each over its rows takes two.
 __device__ __forceinline__ uint32_t or_rows4(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
   const auto a = __builtin_amdgcn_permlane16_swap(w0, w1, false, false);
   const auto b = __builtin_amdgcn_permlane16_swap(w2, w3, false, false);
