@@ -41,11 +41,13 @@ HBM_PEAK_GBS = 8000.0
 # flags (build.COMMON without include paths) to the flags digest.
 _FLAGS = "cfb3b8a417945f0b0125dc066d5529292593229deafe2cb65291c547d733ed6c"
 _FP4 = ("paper_1808_00209_amd/csrc/fp4_expand.hpp",
-        "0e9682bb144ead3c1db16be7650c740fd04372b1500d13fc31e17b78cafc61b4")
+        "e064b7276359145eca018d3f8e8664fded51c0dcf8312e055d85bc9c36130c42")
 _LANE = ("paper_1808_00209_amd/csrc/lane_ops.hpp",
-         "96ece7042c6ed72e9cd799fdd8e007525e30035bbd8d052a9ece380c5e3fda82")
+         "927379b530c4802a6f318cb92dfde891febc3c2eb84a4ff78e17c9f6f93ab879")
 _KERN = ("paper_1808_00209_amd/csrc/kernels.hpp",
-         "7c7597e1eef994edee640fb4fd62722dbf0e527b47da81498e019e6b9cb72943")
+         "ad7d623bea2aea9887f29242cfebc8a97875fa7cc504558f68f729aa4178a362")
+_GEOM = ("paper_1808_00209_amd/csrc/conv_geom.hpp",
+         "c769075ac5ae14cf0322d45cd395cfe1646235090070401b65bfb069e8aef72c")
 MEASURED_TRAFFIC = {
     # profiles/fconv_bconv_cifar_b64.md
     ("cifar_bnn_b64", "L0+L1 fconv+bconv 32x32x3->128->128 k3 pool (fused)"): dict(
@@ -54,18 +56,18 @@ MEASURED_TRAFFIC = {
                        "b9775a39d56ce451c281b54dceafe567d2fc9cc81ff7a7752a4c1a83d8de96f3"),
                       ("paper_1808_00209_amd/csrc/fp32_split.hpp",
                        "7f3a9f6b25af5be34fb5b304976e0225cd491d935c5a4e567bc43c134b6ceb13"),
-                      _FP4, _LANE, _KERN]), flags=_FLAGS),
+                      _FP4, _LANE, _KERN, _GEOM]), flags=_FLAGS),
     # profiles/bconv_mfma_cifar_b64.md
     ("cifar_bnn_b64", "L2+L3 bconv+bconv 16x16x128->256->256 k3 pool (fused)"): dict(
         fetch_kib=858.2, write_kib=128.0, fetch_scale=2.0, write_scale=1.0,
         sources=dict([("paper_1808_00209_amd/csrc/bconv_bconv.hip",
-                       "4967ccbad87efa16575172abf11b76792b74433995d15760fb64a86b724adf26"),
-                      _FP4, _LANE, _KERN]), flags=_FLAGS),
+                       "2439af52051eee9e45fc708d6ec286f418cd55455f28caed1b1446dd02acaa65"),
+                      _FP4, _LANE, _KERN, _GEOM]), flags=_FLAGS),
     ("cifar_bnn_b64", "L5 bconv 8x8x512->512 k3 pool"): dict(
-        fetch_kib=898.1, write_kib=128.0, fetch_scale=2.0, write_scale=1.0,
+        fetch_kib=898.0, write_kib=128.0, fetch_scale=2.0, write_scale=1.0,
         sources=dict([("paper_1808_00209_amd/csrc/bconv_bconv.hip",
-                       "4967ccbad87efa16575172abf11b76792b74433995d15760fb64a86b724adf26"),
-                      _FP4, _LANE, _KERN]), flags=_FLAGS),
+                       "2439af52051eee9e45fc708d6ec286f418cd55455f28caed1b1446dd02acaa65"),
+                      _FP4, _LANE, _KERN, _GEOM]), flags=_FLAGS),
 }
 
 
