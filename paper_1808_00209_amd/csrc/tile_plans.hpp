@@ -1,6 +1,6 @@
-// Launch plans of the tile kernels: which shapes they take and how they cut
-// them.  Pure functions of the sizes, on the host, so that a plan can be
-// looked at (and its bounds checked) without a GPU.
+// Launch plans of the matrix-core conv kernels and the many-row FC kernel: which
+// shapes they take and how they cut them.  Pure functions of the sizes, on the
+// host, so that a plan can be looked at (and its bounds checked) without a GPU.
 #pragma once
 
 #include <stddef.h>
@@ -379,7 +379,8 @@ inline bool conv_tile_plan(const ConvGeom& g, bool sums, bool bits, bool prep, C
   // when pooled (96 -> 192 at 64 x 64 x 120: 26 -> 31 us) or of several chunks
   // (4100 -> 1000 at 4096 rows: 22 -> 44 us).)
   const bool ragged = g.C % 64 != 0, one = g.KH * g.KW == 1;
-  if (g.F <= 32 || (one && (!ragged || g.pool == 2)) || ((!ragged || one) && g.Cw > 8)) return false;
+  if (g.F <= 32 || (one && (!ragged || g.pool == 2)) || ((!ragged || one) && g.Cw > 8))
+    return false;
   // (the k-steps of one chunk: conv_tile_pays)
   if (!ragged && g.KH * g.KW * (g.Cw / 2) < (g.pool == 2 ? 18 : 9)) return false;
   // (units x filter groups, padding aside, are the outputs / 8192)

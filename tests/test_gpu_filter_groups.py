@@ -73,8 +73,8 @@ def test_1x1_filter_groups(case):
     _same(lambda: bnn.bnn_bconv2d(desc, x, w, thr, flip, want_sums=False))
 
 
-@pytest.mark.parametrize("case", [(2, 24, 40, 3, 64, 0), (2, 24, 40, 1, 70, 2), (32, 64, 64, 3, 128, 0)],
-                         ids=str)
+@pytest.mark.parametrize("case", [(2, 24, 40, 3, 64, 0), (2, 24, 40, 1, 70, 2),
+                                  (32, 64, 64, 3, 128, 0)], ids=str)
 @pytest.mark.parametrize("sums", [False, True])
 def test_first_layer_nan_sums_give_bit_0_before_flip(case, sums):
     """S >= thr is false for a NaN sum whatever its sign bit: windows that hold

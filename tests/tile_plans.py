@@ -78,13 +78,13 @@ FIELDS = ("ok ks nchunk wfl Ws strips RS cols items ups units fgs lds H W N Ho W
 
 @functools.lru_cache(maxsize=None)
 def lib():
-    d = tempfile.mkdtemp(prefix="tile_plans_")
-    src, so = os.path.join(d, "shim.cpp"), os.path.join(d, "shim.so")
-    with open(src, "w") as f:
-        f.write(SHIM)
-    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, src, "-o", so],
-                   check=True)
-    h = ctypes.CDLL(so)
+    with tempfile.TemporaryDirectory(prefix="tile_plans_") as d:
+        src, so = os.path.join(d, "shim.cpp"), os.path.join(d, "shim.so")
+        with open(src, "w") as f:
+            f.write(SHIM)
+        subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, src, "-o", so],
+                       check=True)
+        h = ctypes.CDLL(so)
     h.conv_tile_host_us.restype = ctypes.c_double
     return h
 
